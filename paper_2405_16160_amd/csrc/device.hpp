@@ -11,12 +11,15 @@ namespace pdhcg {
 // translation units that include this header
 namespace {
 
-// max that propagates NaN (the hardware max returns the non-NaN operand, which
-// would hide a diverged iterate from the termination test); written with
-// selects only, so that reductions of maxima compile without branches
+// max of two values that are >= +0 or NaN, propagating NaN (the hardware max
+// returns the non-NaN operand, which would hide a diverged iterate from the
+// termination test).  As unsigned integers the bit patterns of such doubles
+// are in the order of their values with every NaN above infinity, so one
+// 64-bit integer compare decides; the FP64 form of this test (two compares for
+// NaN, a compare, an add) made the maxima of a phase its largest cost: an
+// n-side phase of the n = 1000 QP 7.1 us with it.
 __device__ __forceinline__ double maxp(double a, double b) {
-  const double m = a > b ? a : b;
-  return (a != a || b != b) ? a + b : m;  // a + b is NaN when either is
+  return (uint64_t)__double_as_longlong(a) > (uint64_t)__double_as_longlong(b) ? a : b;
 }
 
 // A value that every lane of the wave holds equal, marked as such for the
@@ -98,30 +101,115 @@ __device__ __forceinline__ void block_reduce(double* s, double* mx, double* lds)
   __syncthreads();
 }
 
-// Sum of per-workgroup partials part[slot*nb + j], j < nb, reduced in a
-// fixed order (identical in every workgroup).  NS slots are summed, NM slots
-// maximised; slots are given by index lists.
+// The workgroup's partial results of a phase: NS sums and NM maxima reduced
+// over the workgroup and stored as its partials part[slots[k] * nb + b], sums
+// first.  Only the stored values are needed, so the combination over the waves
+// is done by one lane per value (the waves' results side by side in LDS, read
+// once for all values), not by every thread for every value, and the phase's
+// closing barrier is the one of the grid barrier that follows.  lds holds
+// kWaves * (NS + NM) doubles.
 template <int NS, int NM>
-__device__ __forceinline__ void reduce_partials(const double* part, int nb, const int* sum_slots,
-                                                const int* max_slots, double* s, double* mx, double* lds) {
-  if (nb == 1) {  // one workgroup: its own partial is the total (every thread reads it)
+__device__ __forceinline__ void store_partials(double* s, double* mx, const int (&slots)[NS + NM], double* part, int nb,
+                                               int b, double* lds) {
+  constexpr int W = NS + NM;
 #pragma unroll
-    for (int k = 0; k < NS; ++k) s[k] = part[sum_slots[k]];
+  for (int k = 0; k < NS; ++k) s[k] = group_reduce_last(s[k], kWave, AddOp{});
 #pragma unroll
-    for (int k = 0; k < NM; ++k) mx[k] = part[max_slots[k]];
+  for (int k = 0; k < NM; ++k) mx[k] = group_reduce_last(mx[k], kWave, MaxOp{});
+  const int w = threadIdx.x / kWave;
+  if ((threadIdx.x & (kWave - 1)) == kWave - 1) {
+#pragma unroll
+    for (int k = 0; k < NS; ++k) lds[w * W + k] = s[k];
+#pragma unroll
+    for (int k = 0; k < NM; ++k) lds[w * W + NS + k] = mx[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < W) {
+    const int k = (int)threadIdx.x;
+    double v[kWaves];
+#pragma unroll
+    for (int j = 0; j < kWaves; ++j) v[j] = lds[j * W + k];
+    double a = v[0], m = v[0];
+#pragma unroll
+    for (int j = 1; j < kWaves; ++j) {
+      a += v[j];
+      m = maxp(m, v[j]);
+    }
+    int slot = slots[0];
+#pragma unroll
+    for (int q = 1; q < W; ++q) slot = k == q ? slots[q] : slot;
+    part[slot * nb + b] = k < NS ? a : m;
+  }
+}
+
+// One slot's partials part[0 .. nb) combined by a wave, in the fixed order of
+// its 64-wide segments (the result in the wave's last lane).
+template <typename Op>
+__device__ __forceinline__ double wave_partials(const double* part, int nb, Op op) {
+  constexpr int U = 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  double a = 0.0;
+  for (int j0 = 0; j0 < nb; j0 += U * kWave) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u * kWave + lane;
+      v[u] = j < nb ? part[j] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = group_reduce_last(v[u], kWave, op);
+#pragma unroll
+    for (int u = 0; u < U; ++u) a = op(a, v[u]);
+  }
+  return a;
+}
+
+// the value that a lane of the wave holds, for every lane
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+// NS sums of the per-workgroup partials part[slot * nb + j], j < nb, for every
+// thread: each wave combines them itself from the partials (a few loads and
+// lane moves, no exchange through LDS and no workgroup barrier; at most four
+// values), in the same order in every wave and workgroup.
+template <int NS>
+__device__ __forceinline__ void reduce_sums(const double* part, int nb, const int (&slots)[NS], double* s) {
+  if (nb == 1) {  // one workgroup: its own partial is the total
+#pragma unroll
+    for (int k = 0; k < NS; ++k) s[k] = part[slots[k]];
     return;
   }
 #pragma unroll
-  for (int k = 0; k < NS; ++k) s[k] = 0.0;
+  for (int k = 0; k < NS; ++k) s[k] = wave_partials(part + slots[k] * nb, nb, AddOp{});
 #pragma unroll
-  for (int k = 0; k < NM; ++k) mx[k] = 0.0;
-  for (int j = threadIdx.x; j < nb; j += kBlock) {
+  for (int k = 0; k < NS; ++k) s[k] = lane_value(s[k], kWave - 1);
+}
+
+// NS sums and NM maxima of the partials into out[0 .. NS + NM) (LDS), sums
+// first: the waves of the workgroup take the values in turn.  The caller
+// synchronises the workgroup before reading out.
+template <int NS, int NM>
+__device__ __forceinline__ void reduce_to_lds(const double* part, int nb, const int (&slots)[NS + NM], double* out) {
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  if (nb == 1) {
+    if (threadIdx.x < NS + NM) {
+      int slot = slots[0];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) s[k] += part[sum_slots[k] * nb + j];
-#pragma unroll
-    for (int k = 0; k < NM; ++k) mx[k] = maxp(mx[k], part[max_slots[k] * nb + j]);
+      for (int q = 1; q < NS + NM; ++q) slot = (int)threadIdx.x == q ? slots[q] : slot;
+      out[threadIdx.x] = part[slot];
+    }
+    return;
   }
-  block_reduce<NS, NM>(s, mx, lds);
+#pragma unroll
+  for (int k = 0; k < NS + NM; ++k) {
+    if (k % kWaves != w) continue;
+    const double* p = part + slots[k] * nb;
+    const double v = k < NS ? wave_partials(p, nb, AddOp{}) : wave_partials(p, nb, MaxOp{});
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) out[k] = v;
+  }
 }
 
 // ------------------------------------------------------------ grid barrier

@@ -303,8 +303,7 @@ __device__ __attribute__((noinline)) void dense_cg_spmv(const SolveParams& P, Bl
         P.q[i] = qi;
         s[0] += pi * qi;
       });
-  block_reduce<1, 0>(s, dummy, lds);
-  if (B.tid == 0) P.part[S_PQ * B.nb + B.b] = s[0];
+  store_partials<1, 0>(s, dummy, {S_PQ}, P.part, B.nb, B.b, lds);
 }
 
 // How the n-side pass of a dense Q obtains Q xv: formed into the free CG
@@ -374,15 +373,8 @@ __device__ __attribute__((noinline)) void phase_nside(const SolveParams& P, cons
       epi(i, dense ? rw.q : qxd(i, v[0], rw.x), v[1], rw);
     }
   }
-  block_reduce<3, 3>(s, mx, lds);
-  if (B.tid == 0) {
-    P.part[(slot0 + S_GG) * B.nb + B.b] = s[0];
-    P.part[(slot0 + S_XQX) * B.nb + B.b] = s[1];
-    P.part[(slot0 + S_CX) * B.nb + B.b] = s[2];
-    P.part[(slot0 + S_MG) * B.nb + B.b] = mx[0];
-    P.part[(slot0 + S_MQX) * B.nb + B.b] = mx[1];
-    P.part[(slot0 + S_MATY) * B.nb + B.b] = mx[2];
-  }
+  store_partials<3, 3>(s, mx, {slot0 + S_GG, slot0 + S_XQX, slot0 + S_CX, slot0 + S_MG, slot0 + S_MQX, slot0 + S_MATY},
+                       P.part, B.nb, B.b, lds);
 }
 
 // m-side product u = A xg over the workgroup's rows of pm, with a per-row
@@ -428,12 +420,7 @@ __device__ __forceinline__ void mside_max(const SolveParams& P, double* mx, doub
 }
 
 __device__ void store_mside(const SolveParams& P, Block B, int slot0, double* s1, double* mx, double* lds) {
-  block_reduce<1, 2>(s1, mx, lds);
-  if (B.tid == 0) {
-    P.part[(slot0 + S_MVIOL) * B.nb + B.b] = mx[0];
-    P.part[(slot0 + S_MAX) * B.nb + B.b] = mx[1];
-    P.part[(slot0 + S_BY) * B.nb + B.b] = s1[0];
-  }
+  store_partials<1, 2>(s1, mx, {slot0 + S_BY, slot0 + S_MVIOL, slot0 + S_MAX}, P.part, B.nb, B.b, lds);
 }
 
 // ax = A x and the m-side partials of the current point (start of a solve)
@@ -498,8 +485,7 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
       if (B.tid == 0) epi(i, v[0]);
     }
     double dummy[1] = {0.0};
-    block_reduce<1, 0>(s, dummy, lds);
-    if (B.tid == 0) P.part[S_PQ * B.nb + B.b] = s[0];
+    store_partials<1, 0>(s, dummy, {S_PQ}, P.part, B.nb, B.b, lds);
     return;
   }
   auto epi = [&](int i, double qp) {
@@ -518,8 +504,7 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
     if (B.tid == 0) epi(i, v[0]);
   }
   double dummy[1] = {0.0};
-  block_reduce<1, 0>(s, dummy, lds);
-  if (B.tid == 0) P.part[S_PQ * B.nb + B.b] = s[0];
+  store_partials<1, 0>(s, dummy, {S_PQ}, P.part, B.nb, B.b, lds);
 }
 
 // t = P' v for a low-rank Q = P P' + diag(d): the rows of P' in the
@@ -566,8 +551,7 @@ __device__ __attribute__((noinline)) void phase_cg_update(const SolveParams& P, 
     s[0] += ri * ri;
   }
   double dummy[1] = {0.0};
-  block_reduce<1, 0>(s, dummy, lds);
-  if (B.tid == 0) P.part[S_RR * B.nb + B.b] = s[0];
+  store_partials<1, 0>(s, dummy, {S_RR}, P.part, B.nb, B.b, lds);
 }
 
 // One step of CG in the single-reduction form of Chronopoulos and Gear, as
@@ -736,11 +720,7 @@ __device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block
   else
     run(GatherCG<double>{r_prev, u_prev, s_prev2, alpha, beta, l});
   double dummy[1] = {0.0};
-  block_reduce<2, 0>(s, dummy, lds);
-  if (B.tid == 0) {
-    P.part[S_RR * B.nb + B.b] = s[0];
-    P.part[S_PQ * B.nb + B.b] = s[1];
-  }
+  store_partials<2, 0>(s, dummy, {S_RR, S_PQ}, P.part, B.nb, B.b, lds);
 }
 
 // Dual step and averages (Alg. 1): u = A x^{k+1};
@@ -828,16 +808,7 @@ __device__ __attribute__((noinline)) void phase_dual_trial(const SolveParams& P,
       if (B.tid == 0) epi(i, v[0]);
     }
   }
-  block_reduce<5, 2>(sm, mx, lds);
-  if (B.tid == 0) {
-    P.part[S_TBY * B.nb + B.b] = sm[0];
-    P.part[S_DY2 * B.nb + B.b] = sm[1];
-    P.part[S_DYADX * B.nb + B.b] = sm[2];
-    P.part[S_DX2 * B.nb + B.b] = sm[3];
-    P.part[S_DXQDX * B.nb + B.b] = sm[4];
-    P.part[S_TVIOL * B.nb + B.b] = mx[0];
-    P.part[S_TMAX * B.nb + B.b] = mx[1];
-  }
+  store_partials<5, 2>(sm, mx, {S_TBY, S_DY2, S_DYADX, S_DX2, S_DXQDX, S_TVIOL, S_TMAX}, P.part, B.nb, B.b, lds);
 }
 
 // An accepted trial becomes the iterate: y = y', Ax = A x', the averages take
@@ -899,10 +870,8 @@ __device__ __attribute__((noinline)) void phase_restart(const SolveParams& P, Bl
     if (use_avg) P.ax[i] = P.ax_avg[i];
   }
   double dummy[1] = {0.0};
-  block_reduce<2, 0>(s, dummy, lds);
+  store_partials<2, 0>(s, dummy, {S_DX, S_DY}, P.part, B.nb, B.b, lds);
   if (B.tid == 0) {
-    P.part[S_DX * B.nb + B.b] = s[0];
-    P.part[S_DY * B.nb + B.b] = s[1];
     if (use_avg) {
       P.part[S_MVIOL * B.nb + B.b] = P.part[(S_AVG0 + S_MVIOL) * B.nb + B.b];
       P.part[S_MAX * B.nb + B.b] = P.part[(S_AVG0 + S_MAX) * B.nb + B.b];
@@ -942,47 +911,41 @@ struct Kkt {
   double rp, rd, rg, kkt, pobj, dobj;
 };
 
-__device__ Kkt kkt_from(const double* s, const double* mx, double nb_inf, double nc_inf) {
-  // s: g.g, x.Qx, c.x, b.y ; mx: |g|, |Qx|, |A'y|, (u-b)^+, |u|
-  Kkt k;
-  const double xqx = s[1], cx = s[2], by = s[3];
-  k.rp = rel_div(mx[3], maxp(mx[4], nb_inf));
-  k.rd = rel_div(mx[0], maxp(mx[1], maxp(mx[2], nc_inf)));
-  k.rg = fabs(xqx + cx + by) / (1.0 + maxp(fabs(0.5 * xqx + cx), fabs(0.5 * xqx + by)));
-  k.kkt = maxp(k.rp, maxp(k.rd, k.rg));
-  k.pobj = 0.5 * xqx + cx;
-  k.dobj = -0.5 * xqx - by;
-  return k;
-}
-
 // relKKT pieces from the partials at slot0 (and, when gg / flag are given,
-// g.g and the time-limit flag); thread 0 writes them to *out, *gg, *flag (LDS)
+// g.g and the time-limit flag), written to *out, *gg, *flag (LDS) by the first
+// wave, whose thread 0 may go on with them; the others synchronise before they
+// read.  The waves reduce the ten slots in turn; the three ratios are then
+// formed by one division, a lane each.
 __device__ __attribute__((noinline)) void reduce_kkt(const SolveParams& P, Block B, int slot0, double nb_inf,
                                                      double nc_inf, Kkt* out, double* gg, double* flag,
                                                      double* lds) {
-  const int ss[4] = {slot0 + S_GG, slot0 + S_XQX, slot0 + S_CX, slot0 + S_BY};
-  const int ms[6] = {slot0 + S_MG, slot0 + S_MQX, slot0 + S_MATY, slot0 + S_MVIOL, slot0 + S_MAX, S_FLAG};
-  double s[4], mx[6];
-  reduce_partials<4, 6>(P.part, B.nb, ss, ms, s, mx, lds);
+  reduce_to_lds<4, 6>(P.part, B.nb,
+                      {slot0 + S_GG, slot0 + S_XQX, slot0 + S_CX, slot0 + S_BY, slot0 + S_MG, slot0 + S_MQX,
+                       slot0 + S_MATY, slot0 + S_MVIOL, slot0 + S_MAX, S_FLAG},
+                      lds);
+  __syncthreads();
+  if (B.tid >= kWave) return;
+  const double g2 = lds[0], xqx = lds[1], cx = lds[2], by = lds[3], fl = lds[9];
+  const double po = 0.5 * xqx + cx, dp = 0.5 * xqx + by;
+  double num = lds[7], den = maxp(lds[8], nb_inf);                  // lane 0: primal residual
+  if (B.tid == 1) num = lds[4], den = maxp(lds[5], maxp(lds[6], nc_inf));  // lane 1: dual residual
+  if (B.tid == 2) num = fabs(xqx + cx + by), den = maxp(fabs(po), fabs(dp));  // lane 2: gap
+  const double q = rel_div(num, den);
+  const double rp = lane_value(q, 0), rd = lane_value(q, 1), rg = lane_value(q, 2);
   if (B.tid == 0) {
-    if (gg) *gg = s[0];
-    if (flag) *flag = mx[5];
-    Kkt k = kkt_from(s, mx, nb_inf, nc_inf);
+    double kkt = maxp(rp, maxp(rd, rg));
     // a NaN anywhere in g shows in g.g even where the max would not see it
-    if (!(s[0] == s[0])) k.kkt = s[0];
-    *out = k;
+    if (!(g2 == g2)) kkt = g2;
+    out->rp = rp;
+    out->rd = rd;
+    out->rg = rg;
+    out->kkt = kkt;
+    out->pobj = po;
+    out->dobj = -0.5 * xqx - by;
+    if (gg) *gg = g2;
+    if (flag) *flag = fl;
   }
 }
-
-__device__ __attribute__((noinline)) double reduce_one(const SolveParams& P, Block B, int slot, double* lds) {
-  const int ss[1] = {slot};
-  const int ms[1] = {0};
-  double s[1], mx[1];
-  reduce_partials<1, 0>(P.part, B.nb, ss, ms, s, mx, lds);
-  return s[0];
-}
-
-
 
 // ------------------------------------------------------------- main kernel
 
@@ -1034,6 +997,7 @@ struct Ctl {
   int32_t op, l, steps, have_avg, use_avg, first, cur;
   int32_t xlds;       // the primal step left x of the CG rows in LDS (P.cg_own)
   int32_t retry;      // the n-side pass repeats x^k's for a rejected trial
+  int32_t k_in;       // S.k modulo the evaluation period
   // kept Q x (P.qx): the next n-side pass forms Q x with a product (exact),
   // and whether the current point's relKKT pieces (kc) came from such a pass
   int32_t exact, kc_exact;
@@ -1151,7 +1115,7 @@ __device__ void ctl_after_kkt(const SolveParams& P, Ctl& C) {
     C.op = OP_END;
     return;
   }
-  if (C.S.k > 0 && C.S.k % P.eval_period == 0) {
+  if (C.S.k > 0 && C.k_in == 0) {
     C.op = OP_EVAL;
     return;
   }
@@ -1189,7 +1153,41 @@ __device__ void ctl_after_nside(const SolveParams& P, Ctl& C) {
   ctl_after_kkt(P, C);
 }
 
-// the control step after phase `op` and its reduction (C.rk, C.ra, C.rb);
+// The control step after an n-side pass in its usual course (the point is
+// finite and above the tolerance, no evaluation, limit or repeated trial is
+// due): on to the primal step.  Every input is loaded before the first store,
+// so the one thread that runs it waits for LDS once and not once per field.
+// Returns false, with nothing changed, when the case is another one.
+__device__ __forceinline__ bool control_nside(const SolveParams& P, Ctl& C) {
+  const int32_t retry = C.retry, checked = C.S.start_checked, k_in = C.k_in, exact = C.exact;
+  const double anchor = C.S.K_anchor, kkt = C.kc.kkt, rho = C.rho, tflag = C.tflag, tau = C.S.tau, eps = C.S.eps;
+  const int64_t k = C.S.k, kt = C.S.k_total, formed = C.S.qx_formed;
+  const double tol = P.tol, epsf = P.eps_factor;
+  const int64_t cap = P.max_iters;
+  const bool single = P.u0 != nullptr, kept = P.qx != nullptr, own = P.cg_own != nullptr;
+  const bool usual = !retry && checked && anchor == anchor && kkt > tol && kkt < INFINITY && !(k > 0 && k_in == 0) &&
+                     kt < cap && !(tflag > 0.0) && rho > 0.0;
+  if (!usual) return false;
+  C.S.qx_formed = formed + (!kept || exact ? 1 : 0);
+  C.kc_exact = exact;
+  C.exact = 0;
+  C.have_avg = 0;
+  C.S.eps = eps + epsf * kkt;
+  C.inv_tau = 1.0 / tau;
+  C.steps = 0;
+  C.xlds = single && own;
+  C.gamma = rho;
+  C.alpha = 0.0;
+  C.beta = 0.0;
+  C.first = 1;
+  C.cur = 0;
+  C.l = single ? 0 : 1;
+  C.op = single ? OP_CG : OP_CG_SPMV;
+  return true;
+}
+
+// the control step after phase `op` and its reduction (C.rk or, after an
+// n-side pass, C.kc; C.ra, C.rb, C.rho, C.tflag);
 // kept out of line (it runs on one thread; inlined into the driver it would
 // add to the register pressure of every phase around it)
 __device__ __attribute__((noinline)) void control(const SolveParams& P, Ctl& C, int op) {
@@ -1200,18 +1198,15 @@ __device__ __attribute__((noinline)) void control(const SolveParams& P, Ctl& C, 
       C.op = OP_NSIDE;
       break;
     case OP_NSIDE:
+      if (control_nside(P, C)) break;
       if (!P.qx || C.exact) C.S.qx_formed += 1;
       C.kc_exact = C.exact;
       C.exact = 0;
       if (C.retry) {  // x^k again for a repeated trial: only r_0 is needed
         C.retry = 0;
-        C.rho = r.ra;
         ctl_start_cg(P, C, false);
         break;
       }
-      C.kc = r.rk;
-      C.rho = r.ra;
-      C.tflag = r.rb;
       ctl_after_nside(P, C);
       break;
     case OP_DUAL_TRIAL: {
@@ -1270,6 +1265,7 @@ __device__ __attribute__((noinline)) void control(const SolveParams& P, Ctl& C, 
       C.S.K_anchor = C.Kc;
       C.S.K_prev = INFINITY;
       C.S.k = 0;
+      C.k_in = 0;
       C.S.eps = 0.0;
       C.S.restarts += 1;
       C.have_avg = 0;
@@ -1290,25 +1286,26 @@ __device__ __attribute__((noinline)) void control(const SolveParams& P, Ctl& C, 
       ctl_limit_report(P, C);
       break;
     case OP_CG: {
-      const int l = C.l;
+      const int l = C.l, max_cg = P.max_cg, rule = P.cg_rule;
+      const double gl = r.ra, dl = r.rb, gamma = C.gamma, alpha = C.alpha, tau = C.S.tau, eps = C.S.eps;
       if (l > 0) C.steps = l;
-      if (l >= P.max_cg) {  // the last allowed step only advanced x
+      if (l >= max_cg) {  // the last allowed step only advanced x
         ctl_end_cg(P, C);
         break;
       }
       if (l == 0) {
-        C.alpha = C.gamma / r.rb;
+        C.alpha = gamma / dl;
         C.beta = 0.0;
         C.l = 1;
         break;
       }
-      const double gl = r.ra, dl = r.rb;
-      if ((P.cg_rule == 0 && C.S.tau * sqrt(gl) <= C.S.eps) || !(gl > 0.0)) {
+      if ((rule == 0 && tau * sqrt(gl) <= eps) || !(gl > 0.0)) {
         ctl_end_cg(P, C);
         break;
       }
-      C.beta = gl / C.gamma;
-      C.alpha = gl / (dl - C.beta * gl / C.alpha);
+      const double beta = gl / gamma;
+      C.beta = beta;
+      C.alpha = gl / (dl - beta * gl / alpha);
       C.gamma = gl;
       C.l = l + 1;
       break;
@@ -1318,30 +1315,36 @@ __device__ __attribute__((noinline)) void control(const SolveParams& P, Ctl& C, 
       C.op = OP_CG_UPDATE;
       break;
     case OP_CG_UPDATE: {
-      const double rho_new = r.ra;
-      C.steps = C.l;
-      if (C.l == P.max_cg || (P.cg_rule == 0 && C.S.tau * sqrt(rho_new) <= C.S.eps) || !(rho_new > 0.0)) {
+      const int l = C.l, cur = C.cur, max_cg = P.max_cg, rule = P.cg_rule;
+      const double rho_new = r.ra, rho = C.rho, tau = C.S.tau, eps = C.S.eps;
+      C.steps = l;
+      if (l == max_cg || (rule == 0 && tau * sqrt(rho_new) <= eps) || !(rho_new > 0.0)) {
         ctl_end_cg(P, C);
         break;
       }
-      C.beta = rho_new / C.rho;
+      C.beta = rho_new / rho;
       C.rho = rho_new;
       C.first = 0;
-      C.cur ^= 1;
-      C.l += 1;
+      C.cur = cur ^ 1;
+      C.l = l + 1;
       C.op = OP_CG_SPMV;
       break;
     }
     case OP_DUAL:
-    case OP_COMMIT:
-      C.S.k += 1;
-      C.S.k_total += 1;
-      C.budget -= 1;
+    case OP_COMMIT: {
+      const int64_t k = C.S.k, kt = C.S.k_total, budget = C.budget;
+      const int k_in = C.k_in, period = P.eval_period;
+      const int next = k_in + 1 == period ? 0 : k_in + 1;
+      C.S.k = k + 1;
+      C.S.k_total = kt + 1;
+      C.budget = budget - 1;
+      C.k_in = next;
       // a kept Q x is formed anew at every restart evaluation, so its
       // rounding drift never spans more than eval_period iterations
-      C.exact = C.S.k % P.eval_period == 0;
-      C.op = C.budget > 0 ? OP_NSIDE : OP_END;
+      C.exact = next == 0;
+      C.op = budget > 1 ? OP_NSIDE : OP_END;
       break;
+    }
     default:
       C.op = OP_END;
   }
@@ -1445,17 +1448,11 @@ __device__ __forceinline__ ChainEnd cg_chain(const SolveParams& P, Block B, Grid
     };
     tile_rows_impl(t, pt.group, stage, pre, epi);
     double dummy[1] = {0.0};
-    block_reduce<2, 0>(s2, dummy, lds);
-    if (B.tid == 0) {
-      P.part[S_RR * B.nb + B.b] = s2[0];
-      P.part[S_PQ * B.nb + B.b] = s2[1];
-    }
+    store_partials<2, 0>(s2, dummy, {S_RR, S_PQ}, P.part, B.nb, B.b, lds);
     if (!gs.sync()) return ChainEnd{gs.epoch, 0};
     gather(v_new);  // the next step reads the copy this step wrote
-    const int ss[2] = {S_RR, S_PQ};
-    const int ms[1] = {0};
-    double gd[2], m0[1];
-    reduce_partials<2, 0>(P.part, B.nb, ss, ms, gd, m0, lds);
+    double gd[2];
+    reduce_sums<2>(P.part, B.nb, {S_RR, S_PQ}, gd);
     // the control step of a CG phase (control(), OP_CG) while the chain goes on
     const double gl = uniform(gd[0]), dl = uniform(gd[1]);
     const bool stop = l > 0 && ((P.cg_rule == 0 && tau * sqrt(gl) <= eps) || !(gl > 0.0));
@@ -1501,6 +1498,7 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
     C.retry = 0;
     C.exact = 1;
     C.kc_exact = 0;
+    C.k_in = (int32_t)(C.S.k % P.eval_period);
     C.op = C.S.done || budget <= 0 ? OP_END : (C.S.K_anchor != C.S.K_anchor ? OP_AX_START : OP_NSIDE);
   }
   __syncthreads();
@@ -1619,8 +1617,8 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
     if (!(ok = gs.sync())) break;
     double a = 0.0, b = 0.0;
     switch (op) {
-      case OP_NSIDE:
-        reduce_kkt(P, B, 0, nb_inf, nc_inf, &C.rk, &C.ra, &C.rb, lds);
+      case OP_NSIDE:  // (a repeated trial keeps x^k's relKKT: only r_0.r_0 is needed)
+        reduce_kkt(P, B, 0, nb_inf, nc_inf, C.retry ? &C.rk : &C.kc, &C.rho, C.retry ? &C.rb : &C.tflag, lds);
         break;
       case OP_CERTIFY:
       case OP_LIMIT_AX:
@@ -1631,35 +1629,29 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
         reduce_kkt(P, B, S_AVG0, nb_inf, nc_inf, &C.rk, nullptr, nullptr, lds);
         break;
       case OP_RESTART: {
-        const int ss[2] = {S_DX, S_DY};
-        const int ms[1] = {0};
-        double s2[2], m0[1];
-        reduce_partials<2, 0>(P.part, B.nb, ss, ms, s2, m0, lds);
+        double s2[2];
+        reduce_sums<2>(P.part, B.nb, {S_DX, S_DY}, s2);
         a = s2[0];
         b = s2[1];
         break;
       }
       case OP_CG:
         if (C.l < P.max_cg) {
-          const int ss[2] = {S_RR, S_PQ};
-          const int ms[1] = {0};
-          double gd[2], m0[1];
-          reduce_partials<2, 0>(P.part, B.nb, ss, ms, gd, m0, lds);
+          double gd[2];
+          reduce_sums<2>(P.part, B.nb, {S_RR, S_PQ}, gd);
           a = gd[0];
           b = gd[1];
         }
         break;
       case OP_CG_SPMV:
-        a = reduce_one(P, B, S_PQ, lds);
+        reduce_sums<1>(P.part, B.nb, {S_PQ}, &a);
         break;
       case OP_CG_UPDATE:
-        a = reduce_one(P, B, S_RR, lds);
+        reduce_sums<1>(P.part, B.nb, {S_RR}, &a);
         break;
       case OP_DUAL_TRIAL: {
-        const int ss[4] = {S_DX2, S_DY2, S_DYADX, S_DXQDX};
-        const int ms[1] = {0};
-        double t4[4], m0[1];
-        reduce_partials<4, 0>(P.part, B.nb, ss, ms, t4, m0, lds);
+        double t4[4];
+        reduce_sums<4>(P.part, B.nb, {S_DX2, S_DY2, S_DYADX, S_DXQDX}, t4);
         if (B.tid == 0)
           for (int k = 0; k < 4; ++k) C.rt[k] = t4[k];
         break;
@@ -1668,10 +1660,8 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
         break;
     }
     if (B.tid == 0) {
-      if (op != OP_NSIDE) {  // (the n-side reduction wrote its own scalars)
-        C.ra = a;
-        C.rb = b;
-      }
+      C.ra = a;
+      C.rb = b;
       control(P, C, op);
     }
     __syncthreads();
@@ -1735,13 +1725,10 @@ __device__ bool power_norm(const DevMat& A, const DevMat& At, double* v, double*
     w[j] = vj;
     s[0] += vj * vj;
   }
-  block_reduce<1, 0>(s, dummy, lds);
-  if (B.tid == 0) part[S_PW * B.nb + B.b] = s[0];
+  store_partials<1, 0>(s, dummy, {S_PW}, part, B.nb, B.b, lds);
   if (!gs.sync()) return false;
-  const int ss[1] = {S_PW};
-  const int ms[1] = {0};
-  double tot[1], m0[1];
-  reduce_partials<1, 0>(part, B.nb, ss, ms, tot, m0, lds);
+  double tot[1];
+  reduce_sums<1>(part, B.nb, {S_PW}, tot);
   double scale = 1.0 / sqrt(tot[0]);
   double lam = 0.0;
   for (int it = 0; it < iters; ++it) {
@@ -1776,11 +1763,10 @@ __device__ bool power_norm(const DevMat& A, const DevMat& At, double* v, double*
           sw[0] += vv[0] * vv[0];
         }
       }
-      block_reduce<1, 0>(sw, dummy, lds);
-      if (B.tid == 0) part[S_PW * B.nb + B.b] = sw[0];
+      store_partials<1, 0>(sw, dummy, {S_PW}, part, B.nb, B.b, lds);
     }
     if (!gs.sync()) return false;
-    reduce_partials<1, 0>(part, B.nb, ss, ms, tot, m0, lds);
+    reduce_sums<1>(part, B.nb, {S_PW}, tot);
     lam = sqrt(tot[0]);
     if (!(lam > 0.0)) break;
     scale = 1.0 / lam;
