@@ -156,14 +156,6 @@ int pow2_ceil(double v) {
   return g;
 }
 
-// Row partition for nb workgroups over the rows of one or two matrices with
-// the same rows (rp1, rp2: host row pointers, either may be null): contiguous
-// ranges of near-equal work (entries + 2 per row); rows with more than
-// kLongRow entries listed per workgroup; the other rows cut into tiles of at
-// most tile_nnz_for(block) entries and tile_rows_for(block) rows, block being
-// the workgroup size of the kernel that runs the partition (the LDS tile of
-// its translation unit).  The lane group is the power of two at or above the
-// mean length of the short rows.
 // Tiles of the standalone product: runs of whole rows with at most
 // spmv_stream_tile_nnz() entries and spmv_stream_tile_rows() rows; a row
 // longer than that forms a tile of its own.  4 ints per tile: first row, end
@@ -185,9 +177,17 @@ std::vector<int32_t> stream_tiles(int64_t nrows, const int64_t* rp) {
   return t;
 }
 
+// Row partition for nb workgroups of `block` threads over the rows of one or
+// two matrices with the same rows (rp1, rp2: host row pointers, either may be
+// null): contiguous ranges of near-equal work (entries + 2 per row); rows with
+// more than kLongRow entries listed per workgroup; the other rows cut into wave
+// tiles (internal.hpp).  The tiles of a workgroup are sized to share its work
+// (entries + 4 per row: a row's offsets, inputs and epilogue cost about as much
+// as four entries) equally over its waves, in as few rounds as the tile's limits
+// allow.  The lane group is the power of two at or above the mean length of the
+// short rows.
 HostPart build_part(int64_t nrows, int nb, const int64_t* rp1, const int64_t* rp2, int gscale = 0,
                     int block = kSolveBlock) {
-  const int64_t tile_nnz = tile_nnz_for(block), tile_rows = tile_rows_for(block);
   HostPart P;
   auto len = [&](int64_t i) -> int64_t {
     return (rp1 ? rp1[i + 1] - rp1[i] : 0) + (rp2 ? rp2[i + 1] - rp2[i] : 0);
@@ -214,23 +214,45 @@ HostPart build_part(int64_t nrows, int nb, const int64_t* rp1, const int64_t* rp
   P.long_ptr.assign(nb + 1, 0);
   P.tile_ptr.assign(nb + 1, 0);
   int32_t ntiles = 0;
+  const int waves = block / kWave;
+  std::vector<int32_t> cut;  // first and end row of each tile of a range
   for (int b = 0; b < nb; ++b) {
-    int64_t i = P.bounds[b];
     const int64_t end = P.bounds[b + 1];
-    while (i < end) {
-      if (len(i) > kLongRow) {
-        P.long_rows.push_back((int32_t)i);
-        ++i;
-        continue;
+    int64_t nz = 0, rows = 0;
+    for (int64_t i = P.bounds[b]; i < end; ++i)
+      if (len(i) <= kLongRow) nz += len(i), ++rows;
+    const int64_t rounds = std::max<int64_t>(1, std::max((nz + (int64_t)kTileNnz * waves - 1) / ((int64_t)kTileNnz * waves),
+                                                         (rows + (int64_t)kTileRows * waves - 1) / ((int64_t)kTileRows * waves)));
+    // the equal share, a little more if whole rows leave a tile too many
+    int64_t share = std::max<int64_t>(1, (nz + 4 * rows + rounds * waves - 1) / (rounds * waves));
+    for (int attempt = 0;; ++attempt) {
+      cut.clear();
+      int64_t i = P.bounds[b];
+      while (i < end) {
+        if (len(i) > kLongRow) {
+          ++i;
+          continue;
+        }
+        const int64_t start = i;
+        int64_t acc = 0, work = 0;
+        while (i < end && len(i) <= kLongRow && i - start < kTileRows &&
+               (i == start || (acc + len(i) <= kTileNnz && work + len(i) + 4 <= share))) {
+          acc += len(i);
+          work += len(i) + 4;
+          ++i;
+        }
+        cut.push_back((int32_t)start);
+        cut.push_back((int32_t)i);
       }
-      const int64_t start = i;
-      int64_t acc = 0;
-      while (i < end && len(i) <= kLongRow && acc + len(i) <= tile_nnz && i - start < tile_rows) {
-        acc += len(i);
-        ++i;
-      }
-      const int32_t t[6] = {(int32_t)start, (int32_t)i, (int32_t)(rp1 ? rp1[start] : 0), (int32_t)(rp1 ? rp1[i] : 0),
-                            (int32_t)(rp2 ? rp2[start] : 0), (int32_t)(rp2 ? rp2[i] : 0)};
+      if ((int64_t)cut.size() / 2 <= rounds * waves || attempt == 6) break;
+      share += share / 16 + 1;
+    }
+    for (int64_t i = P.bounds[b]; i < end; ++i)
+      if (len(i) > kLongRow) P.long_rows.push_back((int32_t)i);
+    for (size_t k = 0; k < cut.size(); k += 2) {
+      const int32_t s = cut[k], e = cut[k + 1];
+      const int32_t t[6] = {s, e, (int32_t)(rp1 ? rp1[s] : 0), (int32_t)(rp1 ? rp1[e] : 0),
+                            (int32_t)(rp2 ? rp2[s] : 0), (int32_t)(rp2 ? rp2[e] : 0)};
       P.tiles.insert(P.tiles.end(), t, t + 6);
       ++ntiles;
     }
@@ -296,7 +318,7 @@ struct pdhcg_handle {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   DevPart pn1, pcg, pm, pt;                // parts for the persistent kernels
   std::vector<int32_t> cg_bounds, m_bounds;          // host copies of the pcg / pm row ranges
-  int cg_one_tile = 0;  // every workgroup's CG rows form one tile with no long row
+  int cg_one_round = 0;  // every wave has at most one CG tile, of at most kTileNnz entries, and no row is long
   int64_t l2_bytes = 4 << 20;  // L2 of one XCD (device attribute at create)
   int res_bytes = 0;                                 // dynamic LDS of the last solve launch
   int32_t* stiles[3] = {nullptr, nullptr, nullptr};  // tiles of the standalone products (Q, A, A')
@@ -452,9 +474,11 @@ int plan_grid(pdhcg_handle* h, int nb, int gscale) {
   const HostPart pm = build_part(h->m, nb, arp, nullptr, gscale, h->threads);
   h->cg_bounds = pcg.bounds;
   h->m_bounds = pm.bounds;
-  h->cg_one_tile = 1;
+  h->cg_one_round = pcg.long_rows.empty();
   for (int b = 0; b < nb; ++b)
-    if (pcg.tile_ptr[b + 1] - pcg.tile_ptr[b] != 1 || pcg.long_ptr[b + 1] != pcg.long_ptr[b]) h->cg_one_tile = 0;
+    if (pcg.tile_ptr[b + 1] - pcg.tile_ptr[b] > h->threads / kWave) h->cg_one_round = 0;
+  for (size_t t = 0; t < pcg.tiles.size(); t += 6)
+    if (pcg.tiles[t + 3] - pcg.tiles[t + 2] > kTileNnz) h->cg_one_round = 0;
   if ((rc = upload_part(h, pcg, h->pcg))) return rc;
   if ((rc = upload_part(h, pm, h->pm))) return rc;
   if ((rc = upload_part(h, build_part(h->n, nb, trp, nullptr, gscale, h->threads), h->pt))) return rc;
@@ -588,7 +612,7 @@ int plan_residency(pdhcg_handle* h, SolveParams& p) {
   }
   // the chained CG steps (every workgroup or none: they take the CG decisions
   // themselves, so all must run the same code)
-  p.cg_chain = p.own_cg && p.res_cg && p.res_vbytes == 4 && h->cg_one_tile;
+  p.cg_chain = p.own_cg && p.res_cg && p.res_vbytes == 4 && h->cg_one_round;
   h->res_bytes = (int)total;
   return 0;
 }
@@ -667,7 +691,6 @@ int estimate_norm(pdhcg_handle* h) {
   PowerParams pp{};
   pp.A = h->mat(1);
   pp.At = h->mat(2);
-  pp.v = h->p0;
   pp.w = h->p1;
   pp.u = h->ax_avg;
   pp.part = h->part;
@@ -1043,7 +1066,7 @@ int pdhcg_autotune(pdhcg_handle* h, int32_t iters, int32_t* num_blocks, int32_t*
     h->threads = t;
     if ((rc = set_max_nb(h))) break;
     for (int nb : {64, 128, 256, 512}) {
-      if (nb > h->max_nb) continue;
+      if (nb > h->max_nb || nb > 256 * (kSolveBlock / t)) continue;
       for (int g : {-1, 0, 1}) {
         if ((rc = plan_grid(h, nb, g))) break;
         pdhcg_result r;
@@ -1161,11 +1184,10 @@ bool is_dense(const int64_t* rowptr, int64_t n) {
 // autotuner may pick (index 1 of BatchInst's partitions)
 constexpr int kBatchSizes[2] = {kBatchBlock, kSolveBlock};
 
-void batch_parts(const int64_t* qrp, bool dense, int64_t n, const HostCsr& A, const HostCsr& T, int block,
-                 std::vector<int32_t>& out, int32_t g[4], int64_t off[8]) {
-  const int64_t m = A.nrows;
+void batch_parts(const int64_t* qrp, bool dense, int64_t n, int64_t m, const int64_t* arows, const HostCsr& T,
+                 int block, std::vector<int32_t>& out, int32_t g[4], int64_t off[8]) {
   const int64_t* q = dense ? nullptr : qrp;
-  const int64_t* arp = m ? A.rowptr.data() : nullptr;
+  const int64_t* arp = m ? arows : nullptr;
   const int64_t* trp = m ? T.rowptr.data() : nullptr;
   HostPart p1 = build_part(n, 1, q, trp, 0, block);
   HostPart p2 = build_part(n, 1, q, nullptr, 0, block);
@@ -1497,18 +1519,25 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
   }
   h->off_n[count] = vn_tot;
   h->off_m[count] = vm_tot;
-  // partitions (per distinct (Q, A) pair the lists are identical; built per instance for simplicity)
+  // partitions, once per distinct (Q, A) pair: members that share both share them
+  std::map<std::pair<int, int>, int> part_of;
   for (int i = 0; i < count; ++i) {
     BatchInst& I = inst[i];
+    const auto at = part_of.emplace(std::make_pair(q_first[i], a_first[i]), i);
+    if (!at.second) {
+      const BatchInst& F = inst[at.first->second];
+      for (int z = 0; z < nsizes; ++z) {
+        I.part_off[z] = F.part_off[z];
+        std::copy(std::begin(F.g[z]), std::end(F.g[z]), std::begin(I.g[z]));
+        std::copy(std::begin(F.sub_off[z]), std::end(F.sub_off[z]), std::begin(I.sub_off[z]));
+      }
+      continue;
+    }
     const HostCsr& T = At[a_first[i]];
-    HostCsr Ah;
-    Ah.nrows = As[i].nrows;
-    Ah.ncols = As[i].ncols;
-    Ah.rowptr.assign(As[i].rowptr, As[i].rowptr + As[i].nrows + 1);
     for (int z = 0; z < nsizes; ++z) {
       I.part_off[z] = (int64_t)parts.size();
-      batch_parts(Ls ? nullptr : Qs[q_first[i]].rowptr, I.dense != 0, I.n, Ah, T, kBatchSizes[z], parts, I.g[z],
-                  I.sub_off[z]);
+      batch_parts(Ls ? nullptr : Qs[q_first[i]].rowptr, I.dense != 0, I.n, I.m, As[i].rowptr, T, kBatchSizes[z], parts,
+                  I.g[z], I.sub_off[z]);
     }
   }
   // largest first: estimated work ~ entries of Q plus twice those of A

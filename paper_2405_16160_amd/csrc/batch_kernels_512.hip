@@ -1,5 +1,5 @@
-// The batched kernel at 512 threads per workgroup (one instance per CU, LDS
-// tiles of 4 096 entries and 1 024 rows): the alternative that the batch
+// The batched kernel at 512 threads per workgroup (one instance per CU, eight
+// waves on it): the alternative that the batch
 // autotuner (pdhcg_batch_autotune) times against the 256-thread default of
 // batch_kernels.hip; batches of large instances, which stream their data,
 // can run faster with the wider workgroup.

@@ -102,15 +102,15 @@ __device__ __forceinline__ void block_reduce(double* s, double* mx, double* lds)
 }
 
 // The workgroup's partial results of a phase: NS sums and NM maxima reduced
-// over the workgroup and stored as its partials part[slots[k] * nb + b], sums
+// over the workgroup and stored as its partials part[slot(k) * nb + b], sums
 // first.  Only the stored values are needed, so the combination over the waves
 // is done by one lane per value (the waves' results side by side in LDS, read
 // once for all values), not by every thread for every value, and the phase's
 // closing barrier is the one of the grid barrier that follows.  lds holds
 // kWaves * (NS + NM) doubles.
-template <int NS, int NM>
-__device__ __forceinline__ void store_partials(double* s, double* mx, const int (&slots)[NS + NM], double* part, int nb,
-                                               int b, double* lds) {
+template <int NS, int NM, typename Slot>
+__device__ __forceinline__ void store_partials(double* s, double* mx, const Slot& slot, double* part, int nb, int b,
+                                               double* lds) {
   constexpr int W = NS + NM;
 #pragma unroll
   for (int k = 0; k < NS; ++k) s[k] = group_reduce_last(s[k], kWave, AddOp{});
@@ -135,10 +135,7 @@ __device__ __forceinline__ void store_partials(double* s, double* mx, const int 
       a += v[j];
       m = maxp(m, v[j]);
     }
-    int slot = slots[0];
-#pragma unroll
-    for (int q = 1; q < W; ++q) slot = k == q ? slots[q] : slot;
-    part[slot * nb + b] = k < NS ? a : m;
+    part[slot(k) * nb + b] = k < NS ? a : m;
   }
 }
 
@@ -157,9 +154,10 @@ __device__ __forceinline__ double wave_partials(const double* part, int nb, Op o
       v[u] = j < nb ? part[j] : 0.0;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = group_reduce_last(v[u], kWave, op);
-#pragma unroll
-    for (int u = 0; u < U; ++u) a = op(a, v[u]);
+    for (int u = 0; u < U; ++u) {
+      if (u > 0 && j0 + u * kWave >= nb) break;
+      a = op(a, group_reduce_last(v[u], kWave, op));
+    }
   }
   return a;
 }
@@ -175,8 +173,10 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // thread: each wave combines them itself from the partials (a few loads and
 // lane moves, no exchange through LDS and no workgroup barrier; at most four
 // values), in the same order in every wave and workgroup.
-template <int NS>
-__device__ __forceinline__ void reduce_sums(const double* part, int nb, const int (&slots)[NS], double* s) {
+template <int... SLOTS>
+__device__ __forceinline__ void reduce_sums(const double* part, int nb, double* s) {
+  constexpr int NS = sizeof...(SLOTS);
+  constexpr int slots[NS] = {SLOTS...};
   if (nb == 1) {  // one workgroup: its own partial is the total
 #pragma unroll
     for (int k = 0; k < NS; ++k) s[k] = part[slots[k]];
@@ -188,26 +188,24 @@ __device__ __forceinline__ void reduce_sums(const double* part, int nb, const in
   for (int k = 0; k < NS; ++k) s[k] = lane_value(s[k], kWave - 1);
 }
 
+// a sum or a maximum, by a switch of the wave
+struct SumOrMax {
+  bool sum;
+  __device__ __forceinline__ double operator()(double a, double b) const { return sum ? a + b : maxp(a, b); }
+};
+
 // NS sums and NM maxima of the partials into out[0 .. NS + NM) (LDS), sums
-// first: the waves of the workgroup take the values in turn.  The caller
-// synchronises the workgroup before reading out.
-template <int NS, int NM>
-__device__ __forceinline__ void reduce_to_lds(const double* part, int nb, const int (&slots)[NS + NM], double* out) {
-  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+// first: the waves of the workgroup take the values in turn, in one loop (the
+// ten values of relKKT unrolled were 13 KB of code).  The caller synchronises
+// the workgroup before reading out.
+template <int NS, int NM, typename Slot>
+__device__ __forceinline__ void reduce_to_lds(const double* part, int nb, const Slot& slot, double* out) {
   if (nb == 1) {
-    if (threadIdx.x < NS + NM) {
-      int slot = slots[0];
-#pragma unroll
-      for (int q = 1; q < NS + NM; ++q) slot = (int)threadIdx.x == q ? slots[q] : slot;
-      out[threadIdx.x] = part[slot];
-    }
+    if (threadIdx.x < NS + NM) out[threadIdx.x] = part[slot((int)threadIdx.x)];
     return;
   }
-#pragma unroll
-  for (int k = 0; k < NS + NM; ++k) {
-    if (k % kWaves != w) continue;
-    const double* p = part + slots[k] * nb;
-    const double v = k < NS ? wave_partials(p, nb, AddOp{}) : wave_partials(p, nb, MaxOp{});
+  for (int k = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); k < NS + NM; k += kWaves) {
+    const double v = wave_partials(part + (int64_t)slot(k) * nb, nb, SumOrMax{k < NS});
     if ((threadIdx.x & (kWave - 1)) == kWave - 1) out[k] = v;
   }
 }
@@ -467,119 +465,61 @@ struct GatherDir2 {
   }
 };
 
-// ----------------------------------------------------- LDS-staged tiles
+// ------------------------------------------------------------- wave tiles
+//
+// A sparse product is cut on the host into tiles of whole rows that one wave
+// processes alone: at most kTileNnz entries (8 per lane) and kTileRows rows (2
+// per lane), sized so that the waves of a workgroup get equal shares.  The wave
+// loads the tile's row offsets, the rows' own inputs and its entries in one
+// burst, gathers, parks the products in its own stretch of LDS and sums the
+// rows from there.  A wave's LDS accesses complete in order, so no workgroup
+// barrier is needed anywhere in a tile, and the waves drift apart: one gathers
+// while another sums.  Bound by the latency of that chain (two dependent round
+// trips, then LDS).  Against tiles of the whole workgroup (8 entries per thread
+// always loaded, five workgroup barriers, descriptors by flat loads): n = 1000
+// QP 8.2 -> 6.7 ms for 200 iterations, 600 MPC members in a batch 326 -> 233 ms,
+// the low-rank QP n = 1e5 10.5 -> 8.4 ms for 60 iterations.
+
+// the wave's number in the workgroup and lane, the former in a scalar register
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); }
+__device__ __forceinline__ int lane_id() { return (int)threadIdx.x & (kWave - 1); }
+
+// element k of an array whose start is uniform over the wave and whose byte
+// offset 8 k fits 32 bits (entries and rows of one tile): base in scalar
+// registers, one 32-bit offset per lane
+template <typename T>
+__device__ __forceinline__ T gld_at(const T* base, int k) {
+  return *(const __attribute__((address_space(1))) T*)((const __attribute__((address_space(1))) char*)base +
+                                                       (uint32_t)k * (uint32_t)sizeof(T));
+}
+
+// a pointer or integer that is equal in all lanes, in scalar registers
+template <typename T>
+__device__ __forceinline__ T* uni(T* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (T*)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// order this wave's LDS stores before its following loads by other lanes (the
+// hardware keeps the order; this keeps the compiler from changing it)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 struct TileLds {
-  double prod[kTileNnz];
-  double sum1[kTileRows];
-  double sum2[kTileRows];
-  int32_t rp[kTileRows + 1];
-  int32_t rp2[kTileRows + 1];
-  int32_t wide[kTileRows];  // rows of the tile summed by a whole wave
-  int32_t nwide;
+  double prod[kWaves][kTileNnz];
 };
 
-// the workgroup's single LDS staging area for tiles
+// the workgroup's staging area
 __device__ __forceinline__ TileLds& tile_lds() {
   __shared__ TileLds L;
   return L;
 }
-
-constexpr int kStageUnroll = kTileNnz / kBlock;  // entries per thread: one burst per tile
-constexpr int kRowsPerThread = (kTileRows + 1 + kBlock - 1) / kBlock;
-
-// Stage one tile in LDS with every load of the tile in flight at once:
-// row offsets of up to two matrices (rp1, rp2: rowptr[ra + i] - base), and the
-// entry list [M1 entries z0..z0+nz, M2 entries w0..w0+nw] as products
-// val * g(col) into prod[0 .. nz+nw).  Every load is unconditional (indices
-// are clamped into the tile, surplus lanes repeat the last entry and store
-// nothing), so the index, value and row-pointer loads all issue before the
-// first wait, then all gathers before the next.
-template <typename V, typename G1, typename G2>
-__device__ __forceinline__ void stage_tile(const int32_t* rowptr1, const int32_t* col1, const V* val1, const G1& g1,
-                                           int z0, int nz, const int32_t* rowptr2, const int32_t* col2,
-                                           const V* val2, const G2& g2, int w0, int nw, int ra, int nr,
-                                           int32_t* rp1, int32_t* rp2, double* prod) {
-  const int tid = threadIdx.x;
-  int r1[kRowsPerThread], r2[kRowsPerThread];
-#pragma unroll
-  for (int u = 0; u < kRowsPerThread; ++u) {
-    const int i = min(u * kBlock + tid, nr);
-    r1[u] = rowptr1 ? gld(rowptr1 + ra + i) : 0;
-    r2[u] = rowptr2 ? gld(rowptr2 + ra + i) : 0;
-  }
-  const int ntot = nz + nw;
-  if (ntot > 0) {
-    int c[kStageUnroll];
-    V v[kStageUnroll];
-#pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const int k = min(u * kBlock + tid, ntot - 1);
-      const bool first = k < nz;
-      c[u] = gld(first ? col1 + z0 + k : col2 + w0 + (k - nz));
-      v[u] = gld(first ? val1 + z0 + k : val2 + w0 + (k - nz));
-    }
-    double gv[kStageUnroll];
-#pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const int k = min(u * kBlock + tid, ntot - 1);
-      if constexpr (std::is_same<G1, G2>::value) {
-        const G1 g = k < nz ? g1 : g2;
-        gv[u] = g(c[u]);
-      } else {
-        gv[u] = k < nz ? g1(c[u]) : g2(c[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const int k = u * kBlock + tid;
-      if (k < ntot) prod[k] = (double)v[u] * gv[u];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kRowsPerThread; ++u) {
-    const int i = u * kBlock + tid;
-    if (i <= nr) {
-      if (rowptr1) rp1[i] = r1[u] - z0;
-      if (rowptr2) rp2[i] = r2[u] - w0 + nz;
-    }
-  }
-}
-
-// Lanes per row for a tile's row sums: the partition's group size G, made
-// smaller when the tile has many rows, so that all of its rows are summed in
-// one pass of the workgroup (two when it has more rows than threads); each
-// lane then adds a longer stretch of the row.
-__device__ __forceinline__ int tile_group(int G, int nr) {
-  const int fit = nr > 0 ? kBlock / nr : kBlock;
-  const int g = fit >= 1 ? 1 << (31 - __clz(fit)) : 1;
-  return g < G ? g : G;
-}
-
-// A row longer than this many entries per lane of its group is summed by a
-// whole wave instead (skewed tiles: one long row among many short ones)
-constexpr int kLaneEntries = 8;
-__device__ __forceinline__ int wide_row_len(int G) { return kLaneEntries * G > kWave ? kLaneEntries * G : kWave; }
-
-// sum of prod[k] for k = beg + lane, beg + lane + G, ... < end (two chains)
-__device__ __forceinline__ double lane_row_sum(const double* prod, int beg, int end, int lane, int G) {
-  double a0 = 0.0, a1 = 0.0;
-  int k = beg + lane;
-  for (; k + G < end; k += 2 * G) {
-    a0 += prod[k];
-    a1 += prod[k + G];
-  }
-  if (k < end) a0 += prod[k];
-  return a0 + a1;
-}
-
-constexpr int kEpiRows = kTileRows / kBlock;  // epilogue rows per thread in one tile
-static_assert(kTileRows % kBlock == 0, "tile rows split evenly over the threads");
-
-// The no-op prefetch of tile_rows / tile_rows2.
-struct NoPre {
-  __device__ __forceinline__ int operator()(int) const { return 0; }
-};
 
 // Load through a pointer known to address LDS (ds_read rather than a flat load)
 template <typename T>
@@ -593,186 +533,297 @@ __device__ __forceinline__ void lst(T* p, T v) {
   *(__attribute__((address_space(3))) T*)p = v;
 }
 
-// Stage one tile of a single matrix whose rows of the workgroup are held in
-// LDS (lrp[j] = rowptr[roff + j]; lcol / lval hold the entries from eoff):
-// the same products as stage_tile, with only the gathers going to memory.
-template <typename V, typename G1>
-__device__ __forceinline__ void stage_tile_lds(const int32_t* lrp, int roff, const int32_t* lcol, const V* lval,
-                                               int eoff, const G1& g, int z0, int nz, int ra, int nr, int32_t* rp1,
-                                               double* prod) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int u = 0; u < kRowsPerThread; ++u) {
-    const int i = u * kBlock + tid;
-    if (i <= nr) rp1[i] = lld(lrp + ra + i - roff) - z0;
+// One tile: rows [ra, ra + nr), entries [z0, z0 + nz) of the first matrix and
+// [w0, w0 + nw) of the second (scalars of the wave)
+struct Tile {
+  int ra, nr, z0, nz, w0, nw;
+};
+
+// the six descriptor words of tile t, one per lane (not waited for)
+__device__ __forceinline__ int tile_words(const WgPart& pt, int t) {
+  const int q = min(lane_id(), 5), k = t - pt.t0;
+  return k < kCacheTiles ? lld(pt.tl + 6 * k + q) : gld(pt.tiles + 6 * (int64_t)t + q);
+}
+
+__device__ __forceinline__ Tile tile_of(int words) {
+  const auto w = [&](int k) { return __builtin_amdgcn_readlane(words, k); };
+  const int ra = w(0), z0 = w(2), w0 = w(4);
+  return Tile{ra, w(1) - ra, z0, w(3) - z0, w0, w(5) - w0};
+}
+
+// run(tile) for this wave's tiles of the workgroup's share (tiles wave,
+// wave + kWaves, ...); the next descriptor is on its way while one runs
+template <typename Run>
+__device__ __forceinline__ void for_wave_tiles(const WgPart& pt, const Run& run) {
+  const int t1 = uni(pt.t1);
+  int t = uni(pt.t0) + wave_id();
+  if (t >= t1) return;
+  int words = tile_words(pt, t);
+  for (;;) {
+    const Tile d = tile_of(words);
+    t += kWaves;
+    const bool more = t < t1;
+    if (more) words = tile_words(pt, t);
+    run(d);
+    if (!more) return;
   }
-  if (nz > 0) {
-    int c[kStageUnroll];
-    V v[kStageUnroll];
+}
+
+// Where a tile's row offsets and entries come from: device memory, or the
+// workgroup's rows held in LDS (lrp[j] = rowptr[r0 + j], entries from e0).
+template <typename V_>
+struct MemRows {
+  using V = V_;
+  const int32_t* rowptr;
+  const int32_t* cols;
+  const V* vals;
+  // row offset ra + i, entries z0 + k (ra and z0 uniform, i and k small)
+  __device__ __forceinline__ int rp(int ra, int i) const { return gld_at(rowptr + ra, i); }
+  __device__ __forceinline__ int col(int z0, int k) const { return gld_at(cols + z0, k); }
+  __device__ __forceinline__ V val(int z0, int k) const { return gld_at(vals + z0, k); }
+};
+
+template <typename V_>
+struct LdsRows {
+  using V = V_;
+  const int32_t* lrp;
+  const int32_t* lcol;
+  const V* lval;
+  int r0, e0;
+  __device__ __forceinline__ int rp(int ra, int i) const { return lld(lrp + (ra - r0) + i); }
+  __device__ __forceinline__ int col(int z0, int k) const { return lld(lcol + (z0 - e0) + k); }
+  __device__ __forceinline__ V val(int z0, int k) const { return lld(lval + (z0 - e0) + k); }
+};
+
+// gathers in flight per lane: 8, or what a gather of several vectors declares
+template <typename G, typename = void>
+struct burst_of {
+  static constexpr int value = 8;
+};
+template <typename G>
+struct burst_of<G, std::void_t<decltype(G::kBurst)>> {
+  static constexpr int value = G::kBurst;
+};
+
+// Products val * g(col) of the entries z0 .. z0 + nz - 1 into prod[0 .. nz),
+// nz <= kTileNnz.  Loads are unconditional within a step of two entries per
+// lane (indices clamped into the tile, surplus lanes repeat the last entry and
+// store nothing) and steps beyond the tile's entries are skipped by the whole
+// wave, so the index and value loads all issue before the first wait, then the
+// gathers, and a small tile issues none for entries that it does not have.
+constexpr int kLaneNnz = kTileNnz / kWave;
+template <typename Src, typename G>
+__device__ __forceinline__ void stage(const Src& src, const G& g, int z0, int nz, double* prod) {
+  constexpr int B = burst_of<G>::value;
+  const int lane = lane_id();
+  int c[kLaneNnz];
+  typename Src::V v[kLaneNnz];
 #pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const int k = z0 - eoff + min(u * kBlock + tid, nz - 1);
-      c[u] = lld(lcol + k);
-      v[u] = lld(lval + k);
+  for (int u = 0; u < kLaneNnz; u += 2) {
+    if (u * kWave >= nz) break;
+#pragma unroll
+    for (int q = u; q < u + 2; ++q) {
+      const int k = min(q * kWave + lane, nz - 1);
+      c[q] = src.col(z0, k);
+      v[q] = src.val(z0, k);
     }
-    double gv[kStageUnroll];
+  }
 #pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) gv[u] = g(c[u]);
+  for (int u0 = 0; u0 < kLaneNnz; u0 += B) {
+    double gv[B];
 #pragma unroll
-    for (int u = 0; u < kStageUnroll; ++u) {
-      const int k = u * kBlock + tid;
-      if (k < nz) prod[k] = (double)v[u] * gv[u];
+    for (int u = 0; u < B; u += 2) {
+      if ((u0 + u) * kWave >= nz) break;
+      gv[u] = g(c[u0 + u]);
+      gv[u + 1] = g(c[u0 + u + 1]);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if ((u & 1) == 0 && (u0 + u) * kWave >= nz) break;
+      const int k = (u0 + u) * kWave + lane;
+      if (k < nz) prod[k] = (double)v[u0 + u] * gv[u];
     }
   }
 }
 
-// One tile of a single matrix.  pre(row) loads the row epilogue's own inputs
-// (rows of the tile, indices clamped into it) and is issued together with the
-// tile's staging loads, so those inputs cost no extra memory round trip.  Row
-// sums are formed by G-lane groups from the staged products and parked in LDS;
-// then epi(row, sum, pre(row)) runs with one thread per row.
-// stage(L, ra, nr, z0, nz) fills L.rp and L.prod for the tile
-template <typename Stage, typename Pre, typename Epi>
-__device__ __forceinline__ void tile_rows_impl(const int32_t* t, int G, const Stage& stage, const Pre& pre,
-                                               Epi epi) {
-  TileLds& L = tile_lds();
-  const int ra = t[0], nr = t[1] - t[0], z0 = t[2], nz = t[3] - t[2];
-  using PV = decltype(pre(0));
-  PV pv[kEpiRows];
-  if (nr > 0) {
+// The same for two matrices over the same rows: entries [z0, z0 + nz) of the
+// first, then [w0, w0 + nw) of the second, nz + nw <= kTileNnz, in one burst.
+template <typename S, typename G>
+__device__ __forceinline__ void stage2(const S& s1, const G& g1, int z0, int nz, const S& s2, const G& g2, int w0,
+                                       int nw, double* prod) {
+  const int lane = lane_id(), ntot = nz + nw;
+  const int32_t* const c1 = s1.cols + z0;
+  const int32_t* const c2 = s2.cols + ((int64_t)w0 - nz);
+  const auto* const v1 = s1.vals + z0;
+  const auto* const v2 = s2.vals + ((int64_t)w0 - nz);
+  int c[kLaneNnz];
+  typename S::V v[kLaneNnz];
 #pragma unroll
-    for (int u = 0; u < kEpiRows; ++u) pv[u] = pre(ra + min(u * kBlock + (int)threadIdx.x, nr - 1));
-  }
-  if (threadIdx.x == 0) L.nwide = 0;
-  stage(L, ra, nr, z0, nz);
-  __syncthreads();
-  const int Gt = tile_group(G, nr);
-  const int lane = threadIdx.x & (Gt - 1), ng = kBlock / Gt, wlen = wide_row_len(Gt);
-  for (int base = 0; base < nr; base += ng) {
-    const int i = base + (int)threadIdx.x / Gt;
-    const bool act = i < nr;
-    const bool wide = act && L.rp[i + 1] - L.rp[i] > wlen;
-    double s = 0.0;
-    if (act && !wide) s = lane_row_sum(L.prod, L.rp[i], L.rp[i + 1], lane, Gt);
-    s = group_sum_last(s, Gt);
-    if (act && !wide && lane == Gt - 1) L.sum1[i] = s;
-    if (wide && lane == 0) L.wide[atomicAdd(&L.nwide, 1)] = i;
-  }
-  __syncthreads();
-  const int nw = L.nwide;
-  if (nw > 0) {  // wide rows: one wave each
-    const int ln = threadIdx.x & (kWave - 1);
-    for (int j = (int)threadIdx.x / kWave; j < nw; j += kWaves) {
-      const int i = L.wide[j];
-      double s = lane_row_sum(L.prod, L.rp[i], L.rp[i + 1], ln, kWave);
-      s = group_sum_last(s, kWave);
-      if (ln == kWave - 1) L.sum1[i] = s;
+  for (int u = 0; u < kLaneNnz; u += 2) {
+    if (u * kWave >= ntot) break;
+#pragma unroll
+    for (int q = u; q < u + 2; ++q) {
+      const int k = min(q * kWave + lane, ntot - 1);
+      c[q] = gld((k < nz ? c1 : c2) + k);
+      v[q] = gld((k < nz ? v1 : v2) + k);
     }
-    __syncthreads();
+  }
+  double gv[kLaneNnz];
+#pragma unroll
+  for (int u = 0; u < kLaneNnz; u += 2) {
+    if (u * kWave >= ntot) break;
+#pragma unroll
+    for (int q = u; q < u + 2; ++q) {
+      const int k = min(q * kWave + lane, ntot - 1);
+      gv[q] = gld((k < nz ? g1.v : g2.v) + c[q]);
+    }
   }
 #pragma unroll
-  for (int u = 0; u < kEpiRows; ++u) {
-    const int i = u * kBlock + (int)threadIdx.x;
-    if (i < nr) epi(ra + i, L.sum1[i], pv[u]);
+  for (int u = 0; u < kLaneNnz; ++u) {
+    if ((u & 1) == 0 && u * kWave >= ntot) break;
+    const int k = u * kWave + lane;
+    if (k < ntot) prod[k] = (double)v[u] * gv[u];
   }
-  __syncthreads();
 }
 
-template <typename V, typename Gather, typename Pre, typename Epi>
-__device__ __forceinline__ void tile_rows_pf(const int32_t* rowptr, const int32_t* col, const V* val,
-                                             const int32_t* t, int G, const Gather& g, const Pre& pre, Epi epi) {
-  tile_rows_impl(
-      t, G,
-      [&](TileLds& L, int ra, int nr, int z0, int nz) {
-        stage_tile(rowptr, col, val, g, z0, nz, (const int32_t*)nullptr, col, val, g, z0, 0, ra, nr, L.rp, L.rp2,
-                   L.prod);
-      },
-      pre, epi);
+// sum of prod[k] for k = beg + lane, beg + lane + G, ... < end (two chains)
+__device__ __forceinline__ double lane_row_sum(const double* prod, int beg, int end, int lane, int G) {
+  double a0 = 0.0, a1 = 0.0;
+  int k = beg + lane;
+  for (; k + G < end; k += 2 * G) {
+    a0 += prod[k];
+    a1 += prod[k + G];
+  }
+  if (k < end) a0 += prod[k];
+  return a0 + a1;
 }
 
-// the same over the workgroup's rows held in LDS (see stage_tile_lds)
-template <typename V, typename Gather, typename Pre, typename Epi>
-__device__ __forceinline__ void tile_rows_res(const int32_t* lrp, int roff, const int32_t* lcol, const V* lval,
-                                              int eoff, const int32_t* t, int G, const Gather& g, const Pre& pre,
-                                              Epi epi) {
-  tile_rows_impl(
-      t, G,
-      [&](TileLds& L, int ra, int nr, int z0, int nz) {
-        stage_tile_lds(lrp, roff, lcol, lval, eoff, g, z0, nz, ra, nr, L.rp, L.prod);
-      },
-      pre, epi);
+// A row longer than this many entries per lane of its group is summed by the
+// whole wave instead (skewed tiles: one long row among many short ones)
+constexpr int kLaneEntries = 8;
+__device__ __forceinline__ int wide_row_len(int G) { return kLaneEntries * G > kWave ? kLaneEntries * G : kWave; }
+
+// Lanes per row of a tile: the partition's group size G, at most what lets the
+// wave sum all of the tile's rows at once.
+__device__ __forceinline__ int tile_group(int G, int nr) {
+  const int f = kWave >> (32 - __clz(nr - 1));  // 64 over the power of two at or above nr
+  return f < G ? f : G;
 }
+
+// Row sums of a staged tile: lane group `lane / Gt` sums prod[beg .. end) of
+// its row; the sum is valid in the group's last lane.  act: the group has a row.
+__device__ __forceinline__ double wave_row_sum(const double* prod, int beg, int end, bool act, int Gt) {
+  const int lane = lane_id(), sub = lane & (Gt - 1);
+  const bool wide = act && end - beg > wide_row_len(Gt);
+  double s = 0.0;
+  if (act && !wide) s = lane_row_sum(prod, beg, end, sub, Gt);
+  s = group_sum_last(s, Gt);
+  uint64_t todo = __ballot(wide && sub == Gt - 1);
+  while (todo) {  // wide rows: the whole wave, one after another
+    const int L = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    double t = lane_row_sum(prod, __builtin_amdgcn_readlane(beg, L), __builtin_amdgcn_readlane(end, L), lane, kWave);
+    t = lane_value(group_sum_last(t, kWave), kWave - 1);
+    if (lane == L) s = t;
+  }
+  return s;
+}
+
+// One tile: epi(row, s1, s2, pre(row)) for its rows, each in one lane, s1 and
+// s2 the row's sums over the entries of the first and of the second matrix
+// (TWO; else s2 = 0).  pre(row) loads the row's own inputs (rows of the tile,
+// indices clamped into it) and is issued with the tile's loads, so those inputs
+// cost no memory round trip of their own.  stage_in(prod) parks the products,
+// the first matrix's in prod[0 .. nz), the second's behind them.
+template <bool TWO, typename S1, typename S2, typename Stage, typename Pre, typename Epi>
+__device__ __forceinline__ void tile_rows_staged(const Tile& t, int G, const S1& m1, const S2& m2,
+                                                 const Stage& stage_in, const Pre& pre, Epi& epi) {
+  double* const prod = tile_lds().prod[wave_id()];
+  const int lane = lane_id();
+  const int Gt = tile_group(G, t.nr), lg = 31 - __clz(Gt);
+  const int i = min(lane >> lg, t.nr - 1);
+  const bool act = (lane >> lg) < t.nr;
+  const int b1 = m1.rp(t.ra, i) - t.z0, e1 = m1.rp(t.ra, i + 1) - t.z0;
+  int b2 = 0, e2 = 0;
+  if constexpr (TWO) {
+    b2 = m2.rp(t.ra, i) - t.w0 + t.nz;
+    e2 = m2.rp(t.ra, i + 1) - t.w0 + t.nz;
+  }
+  const auto pv = pre(t.ra, i);
+  stage_in(prod);
+  wave_sync();
+  const double s1 = wave_row_sum(prod, b1, e1, act, Gt);
+  double s2 = 0.0;
+  if constexpr (TWO) s2 = wave_row_sum(prod, b2, e2, act, Gt);
+  if (act && (lane & (Gt - 1)) == Gt - 1) epi(t.ra + i, s1, s2, pv);
+  wave_sync();
+}
+
+// A tile that is one row of more than kTileNnz entries (at most kLongRow):
+// summed straight from memory by the wave; its last lane ends with the row.
+template <typename V, typename Gather>
+__device__ __forceinline__ double wave_long_row(const MemRows<V>& m, int z0, int nz, const Gather& g) {
+  return group_sum_last(row_partial(m.cols, m.vals, z0, z0 + nz, lane_id(), kWave, g), kWave);
+}
+template <typename V, typename Gather>
+__device__ __forceinline__ double wave_long_row(const LdsRows<V>& m, int z0, int nz, const Gather& g) {
+  double s = 0.0;
+  for (int k = z0 + lane_id(); k < z0 + nz; k += kWave) s += (double)m.val(0, k) * g(m.col(0, k));
+  return group_sum_last(s, kWave);
+}
+
+// the rows of the workgroup's tiles of a single matrix, the partition's first or
+// (SECOND: the A' of a partition cut for a dense Q) its second
+template <bool SECOND = false, typename Src, typename Gather, typename Pre, typename Epi>
+__device__ __forceinline__ void part_rows(const WgPart& pt, const Src& src, const Gather& g, const Pre& pre, Epi epi) {
+  const int G = uni(pt.group);
+  for_wave_tiles(pt, [&](const Tile& d) {
+    const Tile t = SECOND ? Tile{d.ra, d.nr, d.w0, d.nw, 0, 0} : d;
+    if (t.nz > kTileNnz) {
+      const auto pv = pre(t.ra, 0);
+      const double s = wave_long_row(src, t.z0, t.nz, g);
+      if (lane_id() == kWave - 1) epi(t.ra, s, pv);
+      return;
+    }
+    auto put = [&](double* prod) {
+      if (t.nz > 0) stage(src, g, t.z0, t.nz, prod);
+    };
+    auto one = [&](int i, double s, double, const auto& pv) { epi(i, s, pv); };
+    tile_rows_staged<false>(t, G, src, src, put, pre, one);
+  });
+}
+
+// The no-op prefetch.
+struct NoPre {
+  __device__ __forceinline__ int operator()(int, int) const { return 0; }
+};
 
 template <typename V, typename Gather, typename Epi>
-__device__ __forceinline__ void tile_rows(const int32_t* rowptr, const int32_t* col, const V* val, const int32_t* t,
-                                          int G, const Gather& g, Epi epi) {
-  tile_rows_pf(rowptr, col, val, t, G, g, NoPre{}, [&](int i, double s, int) { epi(i, s); });
+__device__ __forceinline__ void part_rows(const WgPart& pt, const int32_t* rowptr, const int32_t* col, const V* val,
+                                          const Gather& g, Epi epi) {
+  part_rows(pt, MemRows<V>{uni(rowptr), uni(col), uni(val)}, g, NoPre{}, [&](int i, double s, int) { epi(i, s); });
 }
 
-// One tile of two matrices over the same rows (the stacked [Q | A'] pass):
-// epi(row, sum1, sum2, pre(row)).  M2 may be absent (rowptr2 == nullptr: sum2 = 0).
-template <typename Gather1, typename Gather2, typename Pre, typename Epi>
-__device__ __forceinline__ void tile_rows2(const int32_t* rowptr1, const int32_t* col1, const double* val1,
-                                           const Gather1& g1, const int32_t* rowptr2, const int32_t* col2,
-                                           const double* val2, const Gather2& g2, const int32_t* t, int G,
-                                           const Pre& pre, Epi epi) {
-  TileLds& L = tile_lds();
-  const int ra = t[0], nr = t[1] - t[0];
-  const int z0 = t[2], nz = rowptr1 ? t[3] - t[2] : 0, w0 = t[4], nw = rowptr2 ? t[5] - t[4] : 0;
-  using PV = decltype(pre(0));
-  PV pv[kEpiRows];
-  if (nr > 0) {
-#pragma unroll
-    for (int u = 0; u < kEpiRows; ++u) pv[u] = pre(ra + min(u * kBlock + (int)threadIdx.x, nr - 1));
-  }
-  if (threadIdx.x == 0) L.nwide = 0;
-  stage_tile(rowptr1, col1, val1, g1, z0, nz, rowptr2, col2, val2, g2, w0, nw, ra, nr, L.rp, L.rp2, L.prod);
-  __syncthreads();
-  const int Gt = tile_group(G, nr);
-  const int lane = threadIdx.x & (Gt - 1), ng = kBlock / Gt, wlen = wide_row_len(Gt);
-  auto len1 = [&](int i) { return rowptr1 ? L.rp[i + 1] - L.rp[i] : 0; };
-  auto len2 = [&](int i) { return rowptr2 ? L.rp2[i + 1] - L.rp2[i] : 0; };
-  for (int base = 0; base < nr; base += ng) {
-    const int i = base + (int)threadIdx.x / Gt;
-    const bool act = i < nr;
-    const bool wide = act && (len1(i) > wlen || len2(i) > wlen);
-    double s1 = 0.0, s2 = 0.0;
-    if (act && !wide) {
-      if (rowptr1) s1 = lane_row_sum(L.prod, L.rp[i], L.rp[i + 1], lane, Gt);
-      if (rowptr2) s2 = lane_row_sum(L.prod, L.rp2[i], L.rp2[i + 1], lane, Gt);
+// The rows of the workgroup's tiles of two matrices over the same rows (the
+// stacked [Q | A'] pass): epi(row, sum1, sum2, pre(row)).
+template <typename Pre, typename Epi>
+__device__ __forceinline__ void part_rows2(const WgPart& pt, const MemRows<double>& m1, const GatherVec<double>& g1,
+                                           const MemRows<double>& m2, const GatherVec<double>& g2, const Pre& pre,
+                                           Epi epi) {
+  const int G = uni(pt.group);
+  for_wave_tiles(pt, [&](const Tile& t) {
+    if (t.nz + t.nw > kTileNnz) {
+      const auto pv = pre(t.ra, 0);
+      const double a = wave_long_row(m1, t.z0, t.nz, g1);
+      const double b = wave_long_row(m2, t.w0, t.nw, g2);
+      if (lane_id() == kWave - 1) epi(t.ra, a, b, pv);
+      return;
     }
-    s1 = group_sum_last(s1, Gt);
-    s2 = group_sum_last(s2, Gt);
-    if (act && !wide && lane == Gt - 1) {
-      L.sum1[i] = s1;
-      L.sum2[i] = s2;
-    }
-    if (wide && lane == 0) L.wide[atomicAdd(&L.nwide, 1)] = i;
-  }
-  __syncthreads();
-  const int nwr = L.nwide;
-  if (nwr > 0) {  // wide rows: one wave each
-    const int ln = threadIdx.x & (kWave - 1);
-    for (int j = (int)threadIdx.x / kWave; j < nwr; j += kWaves) {
-      const int i = L.wide[j];
-      double s1 = 0.0, s2 = 0.0;
-      if (rowptr1) s1 = lane_row_sum(L.prod, L.rp[i], L.rp[i + 1], ln, kWave);
-      if (rowptr2) s2 = lane_row_sum(L.prod, L.rp2[i], L.rp2[i + 1], ln, kWave);
-      s1 = group_sum_last(s1, kWave);
-      s2 = group_sum_last(s2, kWave);
-      if (ln == kWave - 1) {
-        L.sum1[i] = s1;
-        L.sum2[i] = s2;
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < kEpiRows; ++u) {
-    const int i = u * kBlock + (int)threadIdx.x;
-    if (i < nr) epi(ra + i, L.sum1[i], L.sum2[i], pv[u]);
-  }
-  __syncthreads();
+    auto put = [&](double* prod) {
+      if (t.nz + t.nw > 0) stage2(m1, g1, t.z0, t.nz, m2, g2, t.w0, t.nw, prod);
+    };
+    tile_rows_staged<true>(t, G, m1, m2, put, pre, epi);
+  });
 }
 
 }  // namespace

@@ -47,11 +47,12 @@ constexpr int kDenseRows = 4;     // rows per thread in one pass of a dense prod
 // groups of `group` lanes (a power of two <= 64).
 //
 // The other rows of a workgroup's range are cut into tiles of at most
-// kTileNnz entries and kTileRows rows: tiles[6*t .. 6*t+5] = first row, end
+// kTileNnz entries and kTileRows rows, or of one row of at most kLongRow, each
+// the work of one wave (device.hpp), near-equal and a multiple of the waves in
+// number where the range allows: tiles[6*t .. 6*t+5] = first row, end
 // row, entry range in the first matrix, entry range in the second matrix (for
 // the stacked [Q | A'] pass; zero otherwise); workgroup w owns tiles
-// tile_ptr[w] .. tile_ptr[w+1]-1.  A tile's products are staged in LDS with
-// all loads in flight at once and then reduced row by row from LDS.
+// tile_ptr[w] .. tile_ptr[w+1]-1.
 struct Part {
   const int32_t* bounds;
   const int32_t* long_ptr;
@@ -67,17 +68,14 @@ __host__ __device__ inline int64_t res_block_bytes(int64_t nrows, int64_t ne, in
   return align16(4 * (nrows + 1)) + align16(4 * ne) + align16((int64_t)vbytes * ne);
 }
 
-// staged products (FP64 in LDS) and rows per tile of a workgroup of `block`
-// threads: 8 entries and 2 rows per thread
-constexpr int tile_nnz_for(int block) { return 8 * block; }
-constexpr int tile_rows_for(int block) { return 2 * block; }
-constexpr int kTileNnz = tile_nnz_for(kBlock);
-constexpr int kTileRows = tile_rows_for(kBlock);
+// entries and rows per wave tile: 8 entries and one row per lane
+constexpr int kTileNnz = 8 * kWave;
+constexpr int kTileRows = kWave;
 
 // One workgroup's share of a Part, cached in LDS when a solve kernel starts:
 // owned rows [r0, r1), tiles t0 .. t1-1 (the first kCacheTiles of them copied
 // into tl), long rows long_rows[l0 .. l1-1].
-constexpr int kCacheTiles = 16;
+constexpr int kCacheTiles = 32;
 struct WgPart {
   int32_t r0, r1, t0, t1, l0, l1, group;
   int32_t e0;               // first entry of row r0 (resident block)
@@ -89,9 +87,6 @@ struct WgPart {
   const int32_t* lcol;
   const void* lval;
   int32_t tl[6 * kCacheTiles];
-  __device__ __forceinline__ const int32_t* tile(int t) const {
-    return t - t0 < kCacheTiles ? tl + 6 * (t - t0) : tiles + 6 * t;
-  }
 };
 
 // Partial-result slots.  Every workgroup writes one value per slot; after a
@@ -209,8 +204,8 @@ struct SolveParams {
   // executing workgroup (set in its LDS copy of this block; null otherwise)
   int32_t own_cg, own_off;
   double* cg_own;
-  // FP32 products, Q rows and CG state in LDS and one CG tile per workgroup in
-  // every workgroup: the CG steps run chained (cg_chain)
+  // FP32 products, Q rows and CG state in LDS and at most one CG tile per wave
+  // in every workgroup: the CG steps run chained (cg_chain)
   int32_t cg_chain;
   double nb_inf, nc_inf;  // ||b||_inf, ||c||_inf of the caller's problem (enter every relKKT)
   // diagonal preconditioning: the data above are D2 Q D2, D1 A D2, D1 b, D2 c
@@ -246,7 +241,6 @@ struct SolveParams {
 
 struct PowerParams {
   DevMat A, At;
-  double* v;     // n
   double* w;     // n
   double* u;     // m
   double* part;

@@ -8,11 +8,11 @@
 
 namespace pdhcg {
 
-__global__ void __launch_bounds__(kBlock) pdhcg_solve_kernel(const SolveParams* __restrict__ Pg) { solve_body(Pg); }
+__global__ void __launch_bounds__(kSolveBlock) pdhcg_solve_kernel(const SolveParams* __restrict__ Pg) { solve_body(Pg); }
 
 // -------------------------------------------------------- power iteration
 
-__global__ void __launch_bounds__(kBlock) pdhcg_power_kernel(PowerParams P) { power_body(P); }
+__global__ void __launch_bounds__(kSolveBlock) pdhcg_power_kernel(PowerParams P) { power_body(P); }
 
 // ------------------------------------------------------ small helper kernels
 

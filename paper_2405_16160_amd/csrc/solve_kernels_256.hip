@@ -1,6 +1,5 @@
 // The cooperative solve kernel and the power iteration compiled for 256-thread
-// workgroups, two per CU (the device code of solver.hpp at that size, LDS
-// tiles of 2 048 entries).
+// workgroups, two per CU (the device code of solver.hpp at that size).
 // The planner takes it for QPs whose gathered vectors stream from the
 // last-level cache (the textbook CG form's sizes): a CU holds eight waves
 // either way, but two workgroups wait apart, so one's gathers stay in flight

@@ -8,6 +8,9 @@
 #include <math.h>
 
 #include "device.hpp"
+#ifndef PDHCG_PHASE
+#define PDHCG_PHASE __attribute__((noinline))
+#endif
 
 namespace pdhcg {
 
@@ -21,6 +24,29 @@ __device__ __forceinline__ double rel_div(double num, double den) { return num /
 
 // (v)^+ that keeps a NaN visible
 __device__ __forceinline__ double pos_part(double v) { return v > 0.0 ? v : (v == v ? 0.0 : v); }
+
+// The slots of one point's relKKT pieces in the order in which they are reduced:
+// the sums g.g, x.Qx, c.x, b.y, then the maxima |g|, |Qx|, |A'y|, (u - b)^+, |u|
+// (a packed table, four bits each: an array indexed by a lane would live in
+// scratch memory)
+__device__ __forceinline__ int kkt_slot(int k) {
+  constexpr int order[9] = {S_GG, S_XQX, S_CX, S_BY, S_MG, S_MQX, S_MATY, S_MVIOL, S_MAX};
+  constexpr uint64_t table = [&] {
+    uint64_t t = 0;
+    for (int q = 0; q < 9; ++q) t |= (uint64_t)order[q] << (4 * q);
+    return t;
+  }();
+  static_assert(S_GG == 0 && S_BY <= 15, "four bits per slot");
+  return (int)((table >> (4 * k)) & 15);
+}
+
+// the trial's slots, sums b.y', dy.dy, dy.(A dx), dx.dx, dx.(Q dx), then the maxima
+__device__ __forceinline__ int trial_slot(int k) {
+  static_assert(S_TMAX == S_TVIOL + 1 && S_TBY == S_TVIOL + 2 && S_DX2 == S_TVIOL + 3 && S_DY2 == S_TVIOL + 4 &&
+                    S_DYADX == S_TVIOL + 5 && S_DXQDX == S_TVIOL + 6, "slot order");
+  constexpr uint32_t table = 2u | 4u << 4 | 5u << 8 | 3u << 12 | 6u << 16 | 0u << 20 | 1u << 24;
+  return S_TVIOL + (int)((table >> (4 * k)) & 15);
+}
 
 // ------------------------------------------------------------------ phases
 
@@ -264,7 +290,7 @@ __device__ void dense_rows(const V* M, const DevMat& Q, double* svec, double* ts
     __syncthreads();
     for (int j = (int)threadIdx.x; j < n; j += kBlock) svec[j] = gen(j, true);
     __syncthreads();
-    double* red = tile_lds().prod;  // no tile is staged during a dense product
+    double* red = &tile_lds().prod[0][0];  // no tile is staged during a dense product
     if constexpr (sizeof(V) == 4) factor_tv4(M, n, k, svec, red, tscr);
     else if (k <= 64) factor_tv<1>(M, n, k, svec, red, tscr);
     else if (k <= 128) factor_tv<2>(M, n, k, svec, red, tscr);
@@ -280,13 +306,13 @@ __device__ void dense_rows(const V* M, const DevMat& Q, double* svec, double* ts
 }
 
 // out = Q xv for a dense Q owned by one workgroup
-__device__ __attribute__((noinline)) void dense_qx(const SolveParams& P, const double* xv, double* svec, double* out) {
+__device__ PDHCG_PHASE void dense_qx(const SolveParams& P, const double* xv, double* svec, double* out) {
   dense_rows(P.Q.val, P.Q, svec, P.lr_t, [&](int j, bool) { return xv[j]; }, [&](int i, double v) { out[i] = v; });
 }
 
 // CG product for a dense Q owned by one workgroup: stage p in LDS, stream Q
 template <typename V>
-__device__ __attribute__((noinline)) void dense_cg_spmv(const SolveParams& P, Block B, const V* qd,
+__device__ PDHCG_PHASE void dense_cg_spmv(const SolveParams& P, Block B, const V* qd,
                                                         const double* pprev, double* pcur, double beta, int first,
                                                         double inv_tau, double* lds, double* svec) {
   double s[1] = {0.0}, dummy[1] = {0.0};
@@ -303,7 +329,7 @@ __device__ __attribute__((noinline)) void dense_cg_spmv(const SolveParams& P, Bl
         P.q[i] = qi;
         s[0] += pi * qi;
       });
-  store_partials<1, 0>(s, dummy, {S_PQ}, P.part, B.nb, B.b, lds);
+  store_partials<1, 0>(s, dummy, [](int) { return S_PQ; }, P.part, B.nb, B.b, lds);
 }
 
 // How the n-side pass of a dense Q obtains Q xv: formed into the free CG
@@ -315,7 +341,7 @@ enum QxMode { QX_INTO_Q = 0, QX_FORM = 1, QX_KEPT = 2 };
 // workgroup's rows of the partition `pt`.  Writes r = -g (and its FP32 copy)
 // when r != null and stores the six n-side partials at slot0.
 template <bool DENSE>
-__device__ __attribute__((noinline)) void phase_nside(const SolveParams& P, const WgPart& pt, Block B, const double* xv,
+__device__ PDHCG_PHASE void phase_nside(const SolveParams& P, const WgPart& pt, Block B, const double* xv,
                             const double* yv, double* r, float* r32, int r32_stride, int slot0, double* lds,
                             double* svec, int qmode = QX_INTO_Q) {
   // dense Q (one workgroup per QP): Q xv first, into q or qx, unless qx is kept
@@ -326,23 +352,30 @@ __device__ __attribute__((noinline)) void phase_nside(const SolveParams& P, cons
   double s[3] = {0.0, 0.0, 0.0};   // g.g, x.Qx, c.x
   double mx[3] = {0.0, 0.0, 0.0};  // |g|, |Qx|, |A'y|
   // a low-rank Q gathers t = P' xv (formed by phase_lr_t) and adds d xv below
-  GatherVec<double> gx{P.lr_d ? P.lr_pt : xv}, gy{yv};
-  auto qxd = [&](int i, double qx, double xi) { return P.lr_d ? qx + gld(P.lr_d + i) * xi : qx; };
+  const double* const lrd = uni(P.lr_d);
+  const GatherVec<double> gx{uni(lrd ? P.lr_pt : xv)}, gy{uni(yv)};
+  auto qxd = [&](int i, double qx, double xi) { return lrd ? qx + gld(lrd + i) * xi : qx; };
   struct Row {
     double c, x, q, d;
   };
   // d = D2_j when the data are preconditioned: the residual maxima are those
   // of the caller's problem, (Qx)_j = (Q~x~)_j / D2_j and likewise A'y and c
-  const double* dn = P.dn;
-  auto pre = [&](int i) {
-    return Row{gld(P.c + i), gld(xv + i), dense ? gld(qsrc + i) : 0.0, dn ? gld(dn + i) : 1.0};
+  const double* const dn = uni(P.dn);
+  const double* const cp = uni(P.c);
+  double* const xprev = uni(P.x_prev);
+  xv = uni(xv);
+  r = uni(r);
+  r32 = uni(r32);
+  const double* const qs = uni(qsrc);
+  auto pre = [&](int ra, int i) {
+    return Row{gld_at(cp + ra, i), gld_at(xv + ra, i), dense ? gld_at(qs + ra, i) : 0.0, dn ? gld_at(dn + ra, i) : 1.0};
   };
   auto epi = [&](int i, double qx, double aty, const Row& rw) {
     const double g = qx + aty + rw.c;
     if (r) {
       gst(r + i, -g);
       if (r32) gst(r32 + (int64_t)r32_stride * i, (float)(-g));
-      if (P.x_prev) gst(P.x_prev + i, rw.x);  // x^k, for the adaptive step's trials
+      if (xprev) gst(xprev + i, rw.x);  // x^k, for the adaptive step's trials
     }
     s[0] += g * g;
     s[1] += rw.x * qx;
@@ -357,10 +390,19 @@ __device__ __attribute__((noinline)) void phase_nside(const SolveParams& P, cons
       mx[2] = maxp(mx[2], fabs(aty));
     }
   };
-  for (int t = pt.t0; t < pt.t1; ++t)
-    tile_rows2(dense ? nullptr : P.Q.rowptr, P.Q.col, P.Q.val, gx, P.m > 0 ? P.At.rowptr : nullptr, P.At.col,
-               P.At.val, gy, pt.tile(t), G, pre,
-               [&](int i, double qx, double aty, const Row& rw) { epi(i, dense ? rw.q : qxd(i, qx, rw.x), aty, rw); });
+  const MemRows<double> mq{uni(P.Q.rowptr), uni(P.Q.col), uni(P.Q.val)}, mt{uni(P.At.rowptr), uni(P.At.col), uni(P.At.val)};
+  if (dense && P.m > 0)
+    part_rows<true>(pt, mt, gy, pre, [&](int i, double aty, const Row& rw) { epi(i, rw.q, aty, rw); });
+  else if (dense)
+    for (int i = pt.r0 + B.tid; i < pt.r1; i += kBlock) {
+      const Row rw = pre(i, 0);
+      epi(i, rw.q, 0.0, rw);
+    }
+  else if (P.m > 0)
+    part_rows2(pt, mq, gx, mt, gy, pre,
+               [&](int i, double qx, double aty, const Row& rw) { epi(i, qxd(i, qx, rw.x), aty, rw); });
+  else
+    part_rows(pt, mq, gx, pre, [&](int i, double qx, const Row& rw) { epi(i, qxd(i, qx, rw.x), 0.0, rw); });
   for (int t = pt.l0; t < pt.l1; ++t) {
     const int i = pt.long_rows[t];
     double v[2] = {dense ? 0.0 : row_partial(P.Q.col, P.Q.val, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, gx),
@@ -369,12 +411,11 @@ __device__ __attribute__((noinline)) void phase_nside(const SolveParams& P, cons
     double dummy[1] = {0.0};
     block_reduce<2, 0>(v, dummy, lds);
     if (B.tid == 0) {
-      const Row rw = pre(i);
+      const Row rw = pre(i, 0);
       epi(i, dense ? rw.q : qxd(i, v[0], rw.x), v[1], rw);
     }
   }
-  store_partials<3, 3>(s, mx, {slot0 + S_GG, slot0 + S_XQX, slot0 + S_CX, slot0 + S_MG, slot0 + S_MQX, slot0 + S_MATY},
-                       P.part, B.nb, B.b, lds);
+  store_partials<3, 3>(s, mx, [&](int k) { return slot0 + kkt_slot(k < 3 ? k : k + 1); }, P.part, B.nb, B.b, lds);
 }
 
 // m-side product u = A xg over the workgroup's rows of pm, with a per-row
@@ -384,20 +425,18 @@ template <typename V, typename Tx, typename Pre, typename Epi>
 __device__ void mside_rows(const SolveParams& P, Block B, const V* aval, const Tx* xg, double* lds,
                            const Pre& pre, Epi epi) {
   const WgPart& pt = P.w_m;
-  GatherVec<Tx> gx{xg};
+  const GatherVec<Tx> gx{uni(xg)};
   const bool res = pt.lcol != nullptr && (int)sizeof(V) == P.res_vbytes;  // rows of A held in LDS
-  for (int t = pt.t0; t < pt.t1; ++t) {
-    if (res)
-      tile_rows_res(pt.lrp, pt.r0, pt.lcol, (const V*)pt.lval, pt.e0, pt.tile(t), pt.group, gx, pre, epi);
-    else
-      tile_rows_pf(P.A.rowptr, P.A.col, aval, pt.tile(t), pt.group, gx, pre, epi);
-  }
+  if (res)
+    part_rows(pt, LdsRows<V>{uni(pt.lrp), uni(pt.lcol), uni((const V*)pt.lval), uni(pt.r0), uni(pt.e0)}, gx, pre, epi);
+  else
+    part_rows(pt, MemRows<V>{uni(P.A.rowptr), uni(P.A.col), uni(aval)}, gx, pre, epi);
   for (int t = pt.l0; t < pt.l1; ++t) {
     const int i = pt.long_rows[t];
     double v[1] = {row_partial(P.A.col, aval, P.A.rowptr[i], P.A.rowptr[i + 1], B.tid, kBlock, gx)};
     double dummy[1] = {0.0};
     block_reduce<1, 0>(v, dummy, lds);
-    if (B.tid == 0) epi(i, v[0], pre(i));
+    if (B.tid == 0) epi(i, v[0], pre(i, 0));
   }
 }
 
@@ -406,11 +445,11 @@ struct MRow {
   double b, y, ax, ya, d;
 };
 
-__device__ __forceinline__ double mrow_scale(const SolveParams& P, int i) { return P.dm ? gld(P.dm + i) : 1.0; }
+__device__ __forceinline__ double mrow_scale(const double* dm, int ra, int i) { return dm ? gld_at(dm + ra, i) : 1.0; }
 
 // the m-side maxima (u - b)^+ and |u| of a row, in the caller's units
-__device__ __forceinline__ void mside_max(const SolveParams& P, double* mx, double u, const MRow& rw) {
-  if (P.dm) {
+__device__ __forceinline__ void mside_max(const double* dm, double* mx, double u, const MRow& rw) {
+  if (dm) {
     mx[0] = maxp(mx[0], pos_part(u - rw.b) / rw.d);
     mx[1] = maxp(mx[1], fabs(u) / rw.d);
   } else {
@@ -420,17 +459,19 @@ __device__ __forceinline__ void mside_max(const SolveParams& P, double* mx, doub
 }
 
 __device__ void store_mside(const SolveParams& P, Block B, int slot0, double* s1, double* mx, double* lds) {
-  store_partials<1, 2>(s1, mx, {slot0 + S_BY, slot0 + S_MVIOL, slot0 + S_MAX}, P.part, B.nb, B.b, lds);
+  store_partials<1, 2>(s1, mx, [&](int k) { return slot0 + kkt_slot(k == 0 ? 3 : k + 6); }, P.part, B.nb, B.b, lds);
 }
 
 // ax = A x and the m-side partials of the current point (start of a solve)
-__device__ __attribute__((noinline)) void phase_ax(const SolveParams& P, Block B, double* lds) {
+__device__ PDHCG_PHASE void phase_ax(const SolveParams& P, Block B, double* lds) {
   double s1[1] = {0.0}, mx[2] = {0.0, 0.0};
+  const double *const bp = uni(P.b), *const yp = uni(P.y), *const dm = uni(P.dm);
+  double* const axp = uni(P.ax);
   mside_rows(
-      P, B, P.A.val, P.x, lds, [&](int i) { return MRow{gld(P.b + i), gld(P.y + i), 0.0, 0.0, mrow_scale(P, i)}; },
+      P, B, P.A.val, P.x, lds, [&](int ra, int i) { return MRow{gld_at(bp + ra, i), gld_at(yp + ra, i), 0.0, 0.0, mrow_scale(dm, ra, i)}; },
       [&](int i, double u, const MRow& rw) {
-        gst(P.ax + i, u);
-        mside_max(P, mx, u, rw);
+        gst(axp + i, u);
+        mside_max(dm, mx, u, rw);
         s1[0] += rw.b * rw.y;
       });
   store_mside(P, B, 0, s1, mx, lds);
@@ -438,14 +479,16 @@ __device__ __attribute__((noinline)) void phase_ax(const SolveParams& P, Block B
 
 // relKKT pieces of the average: n-side at (xa, ya), m-side u = A xa (kept in ax_avg)
 template <bool DENSE>
-__device__ __attribute__((noinline)) void phase_eval_avg(const SolveParams& P, Block B, double* lds, double* svec) {
+__device__ PDHCG_PHASE void phase_eval_avg(const SolveParams& P, Block B, double* lds, double* svec) {
   phase_nside<DENSE>(P, P.w_n1, B, P.xa, P.ya, nullptr, nullptr, 1, S_AVG0, lds, svec);
   double s1[1] = {0.0}, mx[2] = {0.0, 0.0};
+  const double *const bp = uni(P.b), *const yap = uni(P.ya), *const dm = uni(P.dm);
+  double* const axp = uni(P.ax_avg);
   mside_rows(
-      P, B, P.A.val, P.xa, lds, [&](int i) { return MRow{gld(P.b + i), 0.0, 0.0, gld(P.ya + i), mrow_scale(P, i)}; },
+      P, B, P.A.val, P.xa, lds, [&](int ra, int i) { return MRow{gld_at(bp + ra, i), 0.0, 0.0, gld_at(yap + ra, i), mrow_scale(dm, ra, i)}; },
       [&](int i, double u, const MRow& rw) {
-        gst(P.ax_avg + i, u);
-        mside_max(P, mx, u, rw);
+        gst(axp + i, u);
+        mside_max(dm, mx, u, rw);
         s1[0] += rw.b * rw.ya;
       });
   store_mside(P, B, S_AVG0, s1, mx, lds);
@@ -455,7 +498,7 @@ __device__ __attribute__((noinline)) void phase_eval_avg(const SolveParams& P, B
 // q = (Q + I/tau) p with p gathered through gp (GatherDir on the FP64 r and
 // p_prev, or GatherDir2 on the FP32 (r, p) records); partial p.q.
 template <bool DENSE, typename V, typename G>
-__device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Block B, const V* qval, const G gp,
+__device__ PDHCG_PHASE void phase_cg_spmv(const SolveParams& P, Block B, const V* qval, const G gp,
                               const double* pprev, double* pcur, double beta, int first,
                               double inv_tau, double* lds, double* svec) {
   if constexpr (DENSE) {
@@ -476,7 +519,7 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
       P.q[i] = qi;
       s[0] += pi * qi;
     };
-    for (int t = pt.t0; t < pt.t1; ++t) tile_rows(P.Q.rowptr, P.Q.col, qval, pt.tile(t), pt.group, gt, epi);
+    part_rows(pt, P.Q.rowptr, P.Q.col, qval, gt, epi);
     for (int t = pt.l0; t < pt.l1; ++t) {
       const int i = pt.long_rows[t];
       double v[1] = {row_partial(P.Q.col, qval, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, gt)};
@@ -485,7 +528,7 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
       if (B.tid == 0) epi(i, v[0]);
     }
     double dummy[1] = {0.0};
-    store_partials<1, 0>(s, dummy, {S_PQ}, P.part, B.nb, B.b, lds);
+    store_partials<1, 0>(s, dummy, [](int) { return S_PQ; }, P.part, B.nb, B.b, lds);
     return;
   }
   auto epi = [&](int i, double qp) {
@@ -495,7 +538,7 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
     P.q[i] = qi;
     s[0] += pi * qi;
   };
-  for (int t = pt.t0; t < pt.t1; ++t) tile_rows(P.Q.rowptr, P.Q.col, qval, pt.tile(t), pt.group, gp, epi);
+  part_rows(pt, P.Q.rowptr, P.Q.col, qval, gp, epi);
   for (int t = pt.l0; t < pt.l1; ++t) {
     const int i = pt.long_rows[t];
     double v[1] = {row_partial(P.Q.col, qval, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, gp)};
@@ -504,7 +547,7 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
     if (B.tid == 0) epi(i, v[0]);
   }
   double dummy[1] = {0.0};
-  store_partials<1, 0>(s, dummy, {S_PQ}, P.part, B.nb, B.b, lds);
+  store_partials<1, 0>(s, dummy, [](int) { return S_PQ; }, P.part, B.nb, B.b, lds);
 }
 
 // t = P' v for a low-rank Q = P P' + diag(d): the rows of P' in the
@@ -512,14 +555,14 @@ __device__ __attribute__((noinline)) void phase_cg_spmv(const SolveParams& P, Bl
 // n-side pass, the direction p = r + beta p_prev formed at gather time for a
 // CG product); t goes to lr_pt and its FP32 copy to lr_pt32.  No partials.
 template <typename V, typename G>
-__device__ __attribute__((noinline)) void phase_lr_t(const SolveParams& P, Block B, const V* lval, const G g,
+__device__ PDHCG_PHASE void phase_lr_t(const SolveParams& P, Block B, const V* lval, const G g,
                                                      double* lds) {
   const WgPart& pt = P.w_lr;
   auto epi = [&](int c, double t) {
     P.lr_pt[c] = t;
     P.lr_pt32[c] = (float)t;
   };
-  for (int t = pt.t0; t < pt.t1; ++t) tile_rows(P.Lt.rowptr, P.Lt.col, lval, pt.tile(t), pt.group, g, epi);
+  part_rows(pt, P.Lt.rowptr, P.Lt.col, lval, g, epi);
   for (int t = pt.l0; t < pt.l1; ++t) {
     const int c = pt.long_rows[t];
     double v[1] = {row_partial(P.Lt.col, lval, P.Lt.rowptr[c], P.Lt.rowptr[c + 1], B.tid, kBlock, g)};
@@ -532,7 +575,7 @@ __device__ __attribute__((noinline)) void phase_lr_t(const SolveParams& P, Block
 // CG update on the owned rows: x += alpha p, r -= alpha q; partial r.r.
 // With qx kept (a dense Q in the batch), Q x moves with x by linearity:
 // Q x += alpha Q p, Q p = q - p / tau.
-__device__ __attribute__((noinline)) void phase_cg_update(const SolveParams& P, Block B, const double* pcur, double alpha, int mixed,
+__device__ PDHCG_PHASE void phase_cg_update(const SolveParams& P, Block B, const double* pcur, double alpha, int mixed,
                                 double inv_tau, double* lds) {
   const int r0 = P.w_cg.r0, r1 = P.w_cg.r1;
   double s[1] = {0.0};
@@ -551,7 +594,7 @@ __device__ __attribute__((noinline)) void phase_cg_update(const SolveParams& P, 
     s[0] += ri * ri;
   }
   double dummy[1] = {0.0};
-  store_partials<1, 0>(s, dummy, {S_RR}, P.part, B.nb, B.b, lds);
+  store_partials<1, 0>(s, dummy, [](int) { return S_RR; }, P.part, B.nb, B.b, lds);
 }
 
 // One step of CG in the single-reduction form of Chronopoulos and Gear, as
@@ -575,6 +618,7 @@ struct GatherCG {
   const T* s;
   double alpha, beta;
   int l;
+  static constexpr int kBurst = 4;  // three FP64 loads per entry: 8 entries would spill at 128 registers
   // unconditional loads (u and s are always valid buffers; values not used
   // at the current step are discarded by the selects), so that a tile's
   // gathers all issue before the first wait
@@ -613,7 +657,7 @@ struct GatherCG4 {
 // interleaved (r, u, s) rows in mixed precision, or x, r, u, s in FP64.  The
 // FP64 x of mixed precision is written back by the dual step (phase_dual).
 template <typename V, typename T, bool OWN>
-__device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block B, const V* qval, int l,
+__device__ PDHCG_PHASE void phase_cgcg(const SolveParams& P, Block B, const V* qval, int l,
                                                      double alpha, double beta, double inv_tau, int product,
                                                      int mixed, double* lds) {
   const int c = l & 1;
@@ -637,9 +681,12 @@ __device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block
   // values not used at this step are discarded by selects)
   // (with the state in LDS only step 0 prefetches: r_0 and x from device
   // memory; later steps read LDS in the epilogue)
-  auto pre = [&](int i) {
-    if (!OWN) return Row{gld(r_prev + i), gld(u_prev + i), gld(s_prev2 + i), gld(P.p0 + i), gld(P.x + i)};
-    if (l == 0) return Row{gld(r_prev + i), 0.0, 0.0, 0.0, gld(P.x + i)};
+  const double *const rpp = uni(r_prev), *const upp = uni(u_prev), *const spp = uni(s_prev2), *const ppp = uni(P.p0),
+               *const xpp = uni(P.x);
+  auto pre = [&](int ra, int i) {
+    if (!OWN)
+      return Row{gld_at(rpp + ra, i), gld_at(upp + ra, i), gld_at(spp + ra, i), gld_at(ppp + ra, i), gld_at(xpp + ra, i)};
+    if (l == 0) return Row{gld_at(rpp + ra, i), 0.0, 0.0, 0.0, gld_at(xpp + ra, i)};
     return Row{0.0, 0.0, 0.0, 0.0, 0.0};
   };
   struct Own {
@@ -686,7 +733,7 @@ __device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block
     return Own{ri, s1};
   };
   if (!product) {
-    for (int i = ro0 + B.tid; i < ro0 + no; i += kBlock) own(i, pre(i));
+    for (int i = ro0 + B.tid; i < ro0 + no; i += kBlock) own(i, pre(i, 0));
     return;
   }
   auto epi = [&](int i, double qr, const Row& rw) {
@@ -701,18 +748,16 @@ __device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block
   const WgPart& pt = P.w_cg;
   const bool res = pt.lcol != nullptr && (int)sizeof(V) == P.res_vbytes;  // rows of Q held in LDS
   auto run = [&](const auto& g) {
-    for (int t = pt.t0; t < pt.t1; ++t) {
-      if (res)
-        tile_rows_res(pt.lrp, pt.r0, pt.lcol, (const V*)pt.lval, pt.e0, pt.tile(t), pt.group, g, pre, epi);
-      else
-        tile_rows_pf(P.Q.rowptr, P.Q.col, qval, pt.tile(t), pt.group, g, pre, epi);
-    }
+    if (res)
+      part_rows(pt, LdsRows<V>{uni(pt.lrp), uni(pt.lcol), uni((const V*)pt.lval), uni(pt.r0), uni(pt.e0)}, g, pre, epi);
+    else
+      part_rows(pt, MemRows<V>{uni(P.Q.rowptr), uni(P.Q.col), uni(qval)}, g, pre, epi);
     for (int t = pt.l0; t < pt.l1; ++t) {
       const int i = pt.long_rows[t];
       double v[1] = {row_partial(P.Q.col, qval, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, g)};
       double dummy[1] = {0.0};
       block_reduce<1, 0>(v, dummy, lds);
-      if (B.tid == 0) epi(i, v[0], pre(i));
+      if (B.tid == 0) epi(i, v[0], pre(i, 0));
     }
   };
   if constexpr (std::is_same<T, float>::value)
@@ -720,7 +765,7 @@ __device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block
   else
     run(GatherCG<double>{r_prev, u_prev, s_prev2, alpha, beta, l});
   double dummy[1] = {0.0};
-  store_partials<2, 0>(s, dummy, {S_RR, S_PQ}, P.part, B.nb, B.b, lds);
+  store_partials<2, 0>(s, dummy, [](int k) { return k == 0 ? S_RR : S_PQ; }, P.part, B.nb, B.b, lds);
 }
 
 // Dual step and averages (Alg. 1): u = A x^{k+1};
@@ -729,18 +774,20 @@ __device__ __attribute__((noinline)) void phase_cgcg(const SolveParams& P, Block
 // xo: the LDS x of the CG rows when the primal step kept it there (null:
 // device memory holds x); in mixed precision it is written back here.
 template <typename V, typename Tx>
-__device__ __attribute__((noinline)) void phase_dual(const SolveParams& P, Block B, const V* aval, const Tx* xg,
+__device__ PDHCG_PHASE void phase_dual(const SolveParams& P, Block B, const V* aval, const Tx* xg,
                                                      double sigma, double w, const double* xo, double* lds) {
   double s1[1] = {0.0}, mx[2] = {0.0, 0.0};
+  const double *const bp = uni(P.b), *const dm = uni(P.dm);
+  double *const yp = uni(P.y), *const axp = uni(P.ax), *const yap = uni(P.ya);
   mside_rows(
       P, B, aval, xg, lds,
-      [&](int i) { return MRow{gld(P.b + i), gld(P.y + i), gld(P.ax + i), gld(P.ya + i), mrow_scale(P, i)}; },
+      [&](int ra, int i) { return MRow{gld_at(bp + ra, i), gld_at(yp + ra, i), gld_at(axp + ra, i), gld_at(yap + ra, i), mrow_scale(dm, ra, i)}; },
       [&](int i, double u, const MRow& rw) {
         const double yn = pos_part(rw.y + sigma * (2.0 * u - rw.ax - rw.b));
-        gst(P.y + i, yn);
-        gst(P.ax + i, u);
-        gst(P.ya + i, rw.ya + w * (yn - rw.ya));
-        mside_max(P, mx, u, rw);
+        gst(yp + i, yn);
+        gst(axp + i, u);
+        gst(yap + i, rw.ya + w * (yn - rw.ya));
+        mside_max(dm, mx, u, rw);
         s1[0] += rw.b * yn;
       });
   const int r0 = P.w_cg.r0, r1 = P.w_cg.r1;
@@ -772,18 +819,20 @@ struct GatherDiff {
 };
 
 template <bool DENSE, typename V, typename Tx>
-__device__ __attribute__((noinline)) void phase_dual_trial(const SolveParams& P, Block B, const V* aval,
+__device__ PDHCG_PHASE void phase_dual_trial(const SolveParams& P, Block B, const V* aval,
                                                            const Tx* xg, double sigma, double* lds, double* svec) {
   double sm[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // b.y', dy.dy, dy.(u - Ax), dx.dx, dx.(Q dx)
   double mx[2] = {0.0, 0.0};
+  const double *const bp = uni(P.b), *const yp = uni(P.y), *const axp = uni(P.ax), *const dm = uni(P.dm);
+  double *const ytp = uni(P.y_trial), *const atp = uni(P.ax_trial);
   mside_rows(
       P, B, aval, xg, lds,
-      [&](int i) { return MRow{gld(P.b + i), gld(P.y + i), gld(P.ax + i), 0.0, mrow_scale(P, i)}; },
+      [&](int ra, int i) { return MRow{gld_at(bp + ra, i), gld_at(yp + ra, i), gld_at(axp + ra, i), 0.0, mrow_scale(dm, ra, i)}; },
       [&](int i, double u, const MRow& rw) {
         const double yn = pos_part(rw.y + sigma * (2.0 * u - rw.ax - rw.b));
-        gst(P.y_trial + i, yn);
-        gst(P.ax_trial + i, u);
-        mside_max(P, mx, u, rw);
+        gst(ytp + i, yn);
+        gst(atp + i, u);
+        mside_max(dm, mx, u, rw);
         const double dy = yn - rw.y;
         sm[0] += rw.b * yn;
         sm[1] += dy * dy;
@@ -799,7 +848,7 @@ __device__ __attribute__((noinline)) void phase_dual_trial(const SolveParams& P,
   } else {
     const WgPart& pt = P.w_cg;
     const GatherDiff g{P.x, P.x_prev};
-    for (int t = pt.t0; t < pt.t1; ++t) tile_rows(P.Q.rowptr, P.Q.col, P.Q.val, pt.tile(t), pt.group, g, epi);
+    part_rows(pt, P.Q.rowptr, P.Q.col, P.Q.val, g, epi);
     for (int t = pt.l0; t < pt.l1; ++t) {
       const int i = pt.long_rows[t];
       double v[1] = {row_partial(P.Q.col, P.Q.val, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, g)};
@@ -808,13 +857,13 @@ __device__ __attribute__((noinline)) void phase_dual_trial(const SolveParams& P,
       if (B.tid == 0) epi(i, v[0]);
     }
   }
-  store_partials<5, 2>(sm, mx, {S_TBY, S_DY2, S_DYADX, S_DX2, S_DXQDX, S_TVIOL, S_TMAX}, P.part, B.nb, B.b, lds);
+  store_partials<5, 2>(sm, mx, trial_slot, P.part, B.nb, B.b, lds);
 }
 
 // An accepted trial becomes the iterate: y = y', Ax = A x', the averages take
 // it with weight w (Alg. 1), and the trial's m-side partials become those of
 // the current point (each workgroup moves its own).
-__device__ __attribute__((noinline)) void phase_commit(const SolveParams& P, Block B, double w) {
+__device__ PDHCG_PHASE void phase_commit(const SolveParams& P, Block B, double w) {
   const int m0 = P.w_m.r0, m1 = P.w_m.r1;
   for (int i = m0 + B.tid; i < m1; i += kBlock) {
     const double yn = gld(P.y_trial + i), ya = gld(P.ya + i);
@@ -835,7 +884,7 @@ __device__ __attribute__((noinline)) void phase_commit(const SolveParams& P, Blo
 }
 
 // A rejected trial: back to x^k (y and Ax were left as they were).
-__device__ __attribute__((noinline)) void phase_retry(const SolveParams& P, Block B) {
+__device__ PDHCG_PHASE void phase_retry(const SolveParams& P, Block B) {
   const int n0 = P.w_cg.r0, n1 = P.w_cg.r1;
   for (int j = n0 + B.tid; j < n1; j += kBlock) {
     const double xk = gld(P.x_prev + j);
@@ -847,7 +896,7 @@ __device__ __attribute__((noinline)) void phase_retry(const SolveParams& P, Bloc
 // Restart: move to the candidate (average when use_avg), measure the
 // movement from the previous anchor, and make the candidate the new anchor
 // and the new (empty) average.
-__device__ __attribute__((noinline)) void phase_restart(const SolveParams& P, Block B, int use_avg, int mixed, double* lds) {
+__device__ PDHCG_PHASE void phase_restart(const SolveParams& P, Block B, int use_avg, int mixed, double* lds) {
   double s[2] = {0.0, 0.0};
   const int n0 = P.w_cg.r0, n1 = P.w_cg.r1;
   for (int j = n0 + B.tid; j < n1; j += kBlock) {
@@ -870,7 +919,7 @@ __device__ __attribute__((noinline)) void phase_restart(const SolveParams& P, Bl
     if (use_avg) P.ax[i] = P.ax_avg[i];
   }
   double dummy[1] = {0.0};
-  store_partials<2, 0>(s, dummy, {S_DX, S_DY}, P.part, B.nb, B.b, lds);
+  store_partials<2, 0>(s, dummy, [](int k) { return k == 0 ? S_DX : S_DY; }, P.part, B.nb, B.b, lds);
   if (B.tid == 0) {
     if (use_avg) {
       P.part[S_MVIOL * B.nb + B.b] = P.part[(S_AVG0 + S_MVIOL) * B.nb + B.b];
@@ -882,7 +931,7 @@ __device__ __attribute__((noinline)) void phase_restart(const SolveParams& P, Bl
 
 // copy src -> dst on the workgroup's n- and m-slices (returning the average
 // or restoring the anchor at the end of a solve)
-__device__ __attribute__((noinline)) void phase_copy_point(const SolveParams& P, Block B, const double* xs, const double* ys) {
+__device__ PDHCG_PHASE void phase_copy_point(const SolveParams& P, Block B, const double* xs, const double* ys) {
   const int n0 = P.w_cg.r0, n1 = P.w_cg.r1;
   for (int j = n0 + B.tid; j < n1; j += kBlock) P.x[j] = xs[j];
   const int m0 = P.w_m.r0, m1 = P.w_m.r1;
@@ -890,7 +939,7 @@ __device__ __attribute__((noinline)) void phase_copy_point(const SolveParams& P,
 }
 
 // x, y, their averages and anchors, Ax and the FP32 copy of x set to zero
-__device__ __attribute__((noinline)) void phase_zero_point(const SolveParams& P, Block B) {
+__device__ PDHCG_PHASE void phase_zero_point(const SolveParams& P, Block B) {
   const int n0 = P.w_cg.r0, n1 = P.w_cg.r1;
   for (int j = n0 + B.tid; j < n1; j += kBlock) {
     P.x[j] = 0.0;
@@ -916,13 +965,10 @@ struct Kkt {
 // wave, whose thread 0 may go on with them; the others synchronise before they
 // read.  The waves reduce the ten slots in turn; the three ratios are then
 // formed by one division, a lane each.
-__device__ __attribute__((noinline)) void reduce_kkt(const SolveParams& P, Block B, int slot0, double nb_inf,
+__device__ PDHCG_PHASE void reduce_kkt(const SolveParams& P, Block B, int slot0, double nb_inf,
                                                      double nc_inf, Kkt* out, double* gg, double* flag,
                                                      double* lds) {
-  reduce_to_lds<4, 6>(P.part, B.nb,
-                      {slot0 + S_GG, slot0 + S_XQX, slot0 + S_CX, slot0 + S_BY, slot0 + S_MG, slot0 + S_MQX,
-                       slot0 + S_MATY, slot0 + S_MVIOL, slot0 + S_MAX, S_FLAG},
-                      lds);
+  reduce_to_lds<4, 6>(P.part, B.nb, [&](int k) { return k < 9 ? slot0 + kkt_slot(k) : (int)S_FLAG; }, lds);
   __syncthreads();
   if (B.tid >= kWave) return;
   const double g2 = lds[0], xqx = lds[1], cx = lds[2], by = lds[3], fl = lds[9];
@@ -1350,8 +1396,8 @@ __device__ __attribute__((noinline)) void control(const SolveParams& P, Ctl& C, 
   }
 }
 
-// The primal step's CG run as one chain, for a workgroup whose CG rows form
-// one tile, whose rows of Q and CG state are held in LDS, with FP32 products:
+// The primal step's CG run as one chain, for a workgroup with at most one CG
+// tile per wave, whose rows of Q and CG state are held in LDS, with FP32 products:
 // the same product phase per step as phase_cgcg, one grid barrier per step,
 // the same reduction and control step.  What differs is the order after each
 // barrier: the gathers of the next step's product (the interleaved (r, u, s)
@@ -1370,21 +1416,21 @@ struct ChainEnd {
 __device__ __forceinline__ ChainEnd cg_chain(const SolveParams& P, Block B, GridSync gs, Ctl& C,
                                                        double* lds) {
   const WgPart& pt = P.w_cg;
-  const int32_t* t = pt.tile(pt.t0);
-  const int nz = t[3] - t[2];
-  const int zoff = t[2] - pt.e0;  // first entry of the tile in the LDS block
-  const float* lval = (const float*)pt.lval;
-  double* const ob = P.cg_own;
-  const int ro0 = pt.r0, no = pt.r1 - pt.r0;
+  // this wave's tile, if it has one
+  Tile t{0, 0, 0, 0, 0, 0};
+  if (uni(pt.t0) + wave_id() < uni(pt.t1)) t = tile_of(tile_words(pt, uni(pt.t0) + wave_id()));
+  const int nz = t.nz;
+  const LdsRows<float> src{uni(pt.lrp), uni(pt.lcol), uni((const float*)pt.lval), uni(pt.r0), uni(pt.e0)};
+  double* const ob = uni(P.cg_own);
+  const int ro0 = src.r0, no = uni(pt.r1) - ro0;
+  const int G = uni(pt.group);
   const double inv_tau = C.inv_tau;  // fixed within a primal step
-  float4 q[kStageUnroll];
+  constexpr int U = kTileNnz / kWave;
+  float4 q[U];
   auto gather = [&](const float4* v) {  // raw rows of the tile's columns (no wait)
-    if (nz > 0) {
-      int c[kStageUnroll];
 #pragma unroll
-      for (int u = 0; u < kStageUnroll; ++u) c[u] = lld(pt.lcol + zoff + min(u * kBlock + B.tid, nz - 1));
-#pragma unroll
-      for (int u = 0; u < kStageUnroll; ++u) q[u] = gld(v + c[u]);
+    for (int u = 0; u < U; ++u) {
+      if (u * kWave < nz) q[u] = gld(v + src.col(t.z0, min(u * kWave + lane_id(), nz - 1)));
     }
   };
   // the CG coefficients and counters, kept uniform in registers during the
@@ -1396,32 +1442,27 @@ __device__ __forceinline__ ChainEnd cg_chain(const SolveParams& P, Block B, Grid
   gather((l == 0 ? 0 : (l & 1) ^ 1) ? P.v32_1 : P.v32_0);
   for (;;) {
     float4* v_new = (l & 1) ? P.v32_1 : P.v32_0;
-    auto stage = [&](TileLds& L, int ra, int nr, int z0, int nzt) {
+    auto put = [&](double* prod) {
 #pragma unroll
-      for (int u = 0; u < kRowsPerThread; ++u) {
-        const int i = u * kBlock + B.tid;
-        if (i <= nr) L.rp[i] = lld(pt.lrp + ra + i - ro0) - z0;
-      }
-#pragma unroll
-      for (int u = 0; u < kStageUnroll; ++u) {
-        const int k = u * kBlock + B.tid;
-        if (k < nzt) {
+      for (int u = 0; u < U; ++u) {
+        const int k = u * kWave + lane_id();
+        if (k < nz) {
           const double rj = q[u].x, uj = q[u].y, sj = q[u].z;
           const double s1 = l == 1 ? uj : uj + beta * sj;
           const double g = l == 0 ? rj : rj - alpha * s1;
-          L.prod[k] = (double)lld(lval + zoff + k) * g;
+          prod[k] = (double)src.val(t.z0, k) * g;
         }
       }
     };
     struct Row {
       double rp, xp;
     };
-    auto pre = [&](int i) {  // step 0 starts from r_0 and x in device memory
-      if (l == 0) return Row{gld(P.r + i), gld(P.x + i)};
+    auto pre = [&](int ra, int i) {  // step 0 starts from r_0 and x in device memory
+      if (l == 0) return Row{gld_at(P.r + ra, i), gld_at(P.x + ra, i)};
       return Row{0.0, 0.0};
     };
     double s2[2] = {0.0, 0.0};  // gamma_l, delta_l
-    auto epi = [&](int i, double qr, const Row& rw) {
+    auto epi = [&](int i, double qr, double, const Row& rw) {
       double* const o = ob + (i - ro0);
       double ri, s1 = 0.0;
       if (l == 0) {
@@ -1446,13 +1487,13 @@ __device__ __forceinline__ ChainEnd cg_chain(const SolveParams& P, Block B, Grid
       s2[0] += ri * ri;
       s2[1] += ri * ui;
     };
-    tile_rows_impl(t, pt.group, stage, pre, epi);
+    if (t.nr > 0) tile_rows_staged<false>(t, G, src, src, put, pre, epi);
     double dummy[1] = {0.0};
-    store_partials<2, 0>(s2, dummy, {S_RR, S_PQ}, P.part, B.nb, B.b, lds);
+    store_partials<2, 0>(s2, dummy, [](int k) { return k == 0 ? S_RR : S_PQ; }, P.part, B.nb, B.b, lds);
     if (!gs.sync()) return ChainEnd{gs.epoch, 0};
     gather(v_new);  // the next step reads the copy this step wrote
     double gd[2];
-    reduce_sums<2>(P.part, B.nb, {S_RR, S_PQ}, gd);
+    reduce_sums<S_RR, S_PQ>(P.part, B.nb, gd);
     // the control step of a CG phase (control(), OP_CG) while the chain goes on
     const double gl = uniform(gd[0]), dl = uniform(gd[1]);
     const bool stop = l > 0 && ((P.cg_rule == 0 && tau * sqrt(gl) <= eps) || !(gl > 0.0));
@@ -1630,7 +1671,7 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
         break;
       case OP_RESTART: {
         double s2[2];
-        reduce_sums<2>(P.part, B.nb, {S_DX, S_DY}, s2);
+        reduce_sums<S_DX, S_DY>(P.part, B.nb, s2);
         a = s2[0];
         b = s2[1];
         break;
@@ -1638,20 +1679,20 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
       case OP_CG:
         if (C.l < P.max_cg) {
           double gd[2];
-          reduce_sums<2>(P.part, B.nb, {S_RR, S_PQ}, gd);
+          reduce_sums<S_RR, S_PQ>(P.part, B.nb, gd);
           a = gd[0];
           b = gd[1];
         }
         break;
       case OP_CG_SPMV:
-        reduce_sums<1>(P.part, B.nb, {S_PQ}, &a);
+        reduce_sums<S_PQ>(P.part, B.nb, &a);
         break;
       case OP_CG_UPDATE:
-        reduce_sums<1>(P.part, B.nb, {S_RR}, &a);
+        reduce_sums<S_RR>(P.part, B.nb, &a);
         break;
       case OP_DUAL_TRIAL: {
         double t4[4];
-        reduce_sums<4>(P.part, B.nb, {S_DX2, S_DY2, S_DYADX, S_DXQDX}, t4);
+        reduce_sums<S_DX2, S_DY2, S_DYADX, S_DXQDX>(P.part, B.nb, t4);
         if (B.tid == 0)
           for (int k = 0; k < 4; ++k) C.rt[k] = t4[k];
         break;
@@ -1709,37 +1750,41 @@ __device__ void load_params(SolveParams& Ps, const SolveParams* Pg, int b) {
   __syncthreads();
 }
 
+// v_j scaled at gather time
+struct GatherScaled {
+  const double* v;
+  double scale;
+  __device__ __forceinline__ double operator()(int j) const { return gld(v + j) * scale; }
+};
+
 // ||A||_2 by power iteration on A'A (the step-size rule of Thm 2 needs it;
 // the paper does not say how it is obtained): start from
 // v_j = 0.5 + ((j * 40503) mod 1024) / 1024, normalised; each step
 // u = A v, w = A'u, lambda = ||w||, v = w / lambda; ||A|| ~ sqrt(lambda).
-// v, w (n) and u (m) are work vectors; pn partitions the rows of A', pm
-// those of A.  Returns false if a grid barrier failed.
-__device__ bool power_norm(const DevMat& A, const DevMat& At, double* v, double* w, double* u, double* part,
-                           const Part& pn, const Part& pm, int iters, Block B, GridSync& gs, double* lds,
-                           double* out) {
-  const int n0 = pn.bounds[B.b], n1 = pn.bounds[B.b + 1];
+// w (n) and u (m) are work vectors, v is w scaled where it is gathered; wn is
+// the workgroup's share of the rows of A', wm that of A.  Returns false if a
+// grid barrier failed.
+__device__ bool power_norm(const DevMat& A, const DevMat& At, double* w, double* u, double* part, const WgPart& wn,
+                           const WgPart& wm, int iters, Block B, GridSync& gs, double* lds, double* out) {
+  const int n0 = uni(wn.r0), n1 = uni(wn.r1);
   double s[1] = {0.0}, dummy[1] = {0.0};
   for (int j = n0 + B.tid; j < n1; j += kBlock) {
     const double vj = 0.5 + (double)(((uint64_t)j * 40503ull) % 1024ull) / 1024.0;
     w[j] = vj;
     s[0] += vj * vj;
   }
-  store_partials<1, 0>(s, dummy, {S_PW}, part, B.nb, B.b, lds);
+  store_partials<1, 0>(s, dummy, [](int) { return S_PW; }, part, B.nb, B.b, lds);
   if (!gs.sync()) return false;
   double tot[1];
-  reduce_sums<1>(part, B.nb, {S_PW}, tot);
+  reduce_sums<S_PW>(part, B.nb, tot);
   double scale = 1.0 / sqrt(tot[0]);
   double lam = 0.0;
   for (int it = 0; it < iters; ++it) {
-    for (int j = n0 + B.tid; j < n1; j += kBlock) v[j] = w[j] * scale;
-    if (!gs.sync()) return false;
     {  // u = A v
-      GatherVec<double> gv{v};
-      for (int t = pm.tile_ptr[B.b]; t < pm.tile_ptr[B.b + 1]; ++t)
-        tile_rows(A.rowptr, A.col, A.val, pm.tiles + 6 * t, pm.group, gv, [&](int i, double su) { u[i] = su; });
-      for (int t = pm.long_ptr[B.b]; t < pm.long_ptr[B.b + 1]; ++t) {
-        const int i = pm.long_rows[t];
+      const GatherScaled gv{w, scale};
+      part_rows(wm, A.rowptr, A.col, A.val, gv, [&](int i, double su) { u[i] = su; });
+      for (int t = wm.l0; t < wm.l1; ++t) {
+        const int i = wm.long_rows[t];
         double vv[1] = {row_partial(A.col, A.val, A.rowptr[i], A.rowptr[i + 1], B.tid, kBlock, gv)};
         block_reduce<1, 0>(vv, dummy, lds);
         if (B.tid == 0) u[i] = vv[0];
@@ -1749,13 +1794,12 @@ __device__ bool power_norm(const DevMat& A, const DevMat& At, double* v, double*
     {  // w = A'u, partial ||w||^2
       GatherVec<double> gu{u};
       double sw[1] = {0.0};
-      for (int t = pn.tile_ptr[B.b]; t < pn.tile_ptr[B.b + 1]; ++t)
-        tile_rows(At.rowptr, At.col, At.val, pn.tiles + 6 * t, pn.group, gu, [&](int i, double st) {
-          w[i] = st;
-          sw[0] += st * st;
-        });
-      for (int t = pn.long_ptr[B.b]; t < pn.long_ptr[B.b + 1]; ++t) {
-        const int i = pn.long_rows[t];
+      part_rows(wn, At.rowptr, At.col, At.val, gu, [&](int i, double st) {
+        w[i] = st;
+        sw[0] += st * st;
+      });
+      for (int t = wn.l0; t < wn.l1; ++t) {
+        const int i = wn.long_rows[t];
         double vv[1] = {row_partial(At.col, At.val, At.rowptr[i], At.rowptr[i + 1], B.tid, kBlock, gu)};
         block_reduce<1, 0>(vv, dummy, lds);
         if (B.tid == 0) {
@@ -1763,10 +1807,10 @@ __device__ bool power_norm(const DevMat& A, const DevMat& At, double* v, double*
           sw[0] += vv[0] * vv[0];
         }
       }
-      store_partials<1, 0>(sw, dummy, {S_PW}, part, B.nb, B.b, lds);
+      store_partials<1, 0>(sw, dummy, [](int) { return S_PW; }, part, B.nb, B.b, lds);
     }
     if (!gs.sync()) return false;
-    reduce_sums<1>(part, B.nb, {S_PW}, tot);
+    reduce_sums<S_PW>(part, B.nb, tot);
     lam = sqrt(tot[0]);
     if (!(lam > 0.0)) break;
     scale = 1.0 / lam;
@@ -1850,6 +1894,7 @@ __device__ __forceinline__ void batch_solve(const BatchParams& BP) {
   // are read back only by the same workgroup, after a workgroup barrier
   __shared__ double part_lds[NSLOT];
   load_params(Ps, BP.params + idx, 0);
+  fill_wg_part(Ps.w_lr, Ps.pt, 0);  // (a batch has no sparse low-rank Q: the share of A' for the power iteration)
   if (threadIdx.x == 0) {  // this solve's partials, start point and warm-start fallback
     Ps.part = part_lds;
     const uint32_t gv = BP.given ? BP.given[idx] : 0u;
@@ -1877,7 +1922,7 @@ __device__ __forceinline__ void batch_solve(const BatchParams& BP) {
   }
   __syncthreads();
   double nrm = 0.0;
-  if (P.m > 0) power_norm(P.A, P.At, P.p0, P.p1, P.ax_avg, P.part, P.pt, P.pm, BP.power_iters, B, gs, lds, &nrm);
+  if (P.m > 0) power_norm(P.A, P.At, P.p1, P.ax_avg, P.part, P.w_lr, P.w_m, BP.power_iters, B, gs, lds, &nrm);
   __shared__ Ctl C;
   if (B.tid == 0) {
     SolverState& S = C.S;
@@ -1907,9 +1952,12 @@ __device__ __forceinline__ void power_body(const PowerParams& P) {
   Block B{(int)blockIdx.x, (int)gridDim.x, (int)threadIdx.x};
   GridSync gs{P.bar, (uint32_t)gridDim.x, 0};
   if (!gs.init()) return;  // (the host finds the abort word raised)
+  __shared__ WgPart wn, wm;
+  fill_wg_part(wn, P.pn, B.b);
+  fill_wg_part(wm, P.pm, B.b);
+  __syncthreads();
   double nrm = 0.0;
-  if (power_norm(P.A, P.At, P.v, P.w, P.u, P.part, P.pn, P.pm, P.iters, B, gs, lds, &nrm) && B.b == 0 &&
-      B.tid == 0)
+  if (power_norm(P.A, P.At, P.w, P.u, P.part, wn, wm, P.iters, B, gs, lds, &nrm) && B.b == 0 && B.tid == 0)
     P.out[0] = nrm;
 }
 
