@@ -1261,6 +1261,7 @@ struct pdhcg_batch {
   hipStream_t stream = nullptr;
   pdhcg_settings s{};
   bool pre = false, mixed = false;
+  bool any_dense = false;            // an instance's Q is dense or factored
   int32_t nsizes = 1;                // workgroup sizes with partitions built (2: the autotuner may switch)
   int32_t threads = kBatchBlock;     // threads per workgroup of the batched kernel
   DevBuf D;
@@ -1578,6 +1579,7 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
   const bool adaptive = s->step_rule == 1;
   bool any_dense = false;
   for (int i = 0; i < count; ++i) any_dense |= inst[i].dense != 0;
+  h->any_dense = any_dense;
   for (int k = 0; k < 10; ++k) {
     nv[k] = nullptr;
     if ((k == 7 && !adaptive) || (k == 8 && !Ls) || (k == 9 && (adaptive || !any_dense))) continue;
@@ -1789,7 +1791,8 @@ hipError_t launch_batch(pdhcg_batch* h, hipStream_t stream) {
   bp.params = h->d_params + (size_t)z * h->count;
   hipError_t e = launch_batch_clock(bp.t0, stream);
   if (e != hipSuccess) return e;
-  return z ? launch_batch_512(bp, h->count, stream) : launch_batch_256(bp, h->count, stream);
+  if (z) return launch_batch_512(bp, h->count, stream);
+  return h->any_dense ? launch_batch_256(bp, h->count, stream) : launch_batch_sparse(bp, h->count, stream);
 }
 
 // Solve every instance of a packed batch.  x0 / y0: packed start points

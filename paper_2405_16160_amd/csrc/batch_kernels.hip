@@ -15,7 +15,7 @@ namespace pdhcg {
 // kernel and every function it calls to two waves per SIMD (256 registers),
 // the budget at which two workgroups fit on a CU; with the bound of the
 // launch size alone the compiler takes the whole register file.
-__global__ void __launch_bounds__(kSolveBlock) pdhcg_batch_kernel(BatchParams BP) { batch_solve(BP); }
+__global__ void __launch_bounds__(kSolveBlock) pdhcg_batch_kernel(BatchParams BP) { batch_solve<true>(BP); }
 
 __global__ void batch_clock_kernel(uint64_t* t0) {
   if (threadIdx.x == 0) *t0 = wall_clock64();

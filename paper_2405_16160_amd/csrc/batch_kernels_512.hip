@@ -8,7 +8,7 @@
 
 namespace pdhcg {
 
-__global__ void __launch_bounds__(kSolveBlock) pdhcg_batch_kernel_wg512(BatchParams BP) { batch_solve(BP); }
+__global__ void __launch_bounds__(kSolveBlock) pdhcg_batch_kernel_wg512(BatchParams BP) { batch_solve<true>(BP); }
 
 hipError_t launch_batch_512(const BatchParams& p, int count, hipStream_t s) {
   hipLaunchKernelGGL(pdhcg_batch_kernel_wg512, dim3(count), dim3(kBlock), 0, s, p);

@@ -282,10 +282,12 @@ int solve_batch_in_region(int32_t count, const pdhcg_csr* Qs, const pdhcg_csr* A
                           double* const* x_outs, double* const* y_outs, pdhcg_result* rs, const pdhcg_settings* s,
                           void* hip_stream, char* region, size_t region_bytes);
 
-// the batched kernel with 256 (batch_kernels.hip) or 512 threads per
-// workgroup (batch_kernels_512.hip); the clock kernel stamps the batch's start
+// the batched kernel with 256 (batch_kernels.hip; batch_kernels_sparse.hip when
+// every Q is sparse) or 512 threads per workgroup (batch_kernels_512.hip); the
+// clock kernel stamps the batch's start
 hipError_t launch_batch_clock(uint64_t* t0, hipStream_t s);
 hipError_t launch_batch_256(const BatchParams& p, int count, hipStream_t s);
+hipError_t launch_batch_sparse(const BatchParams& p, int count, hipStream_t s);
 hipError_t launch_batch_512(const BatchParams& p, int count, hipStream_t s);
 // the cooperative kernels at `threads` per workgroup (512: solve_kernels.hip;
 // 256: solve_kernels_256.hip, whose kernels solve_kernel_256() and

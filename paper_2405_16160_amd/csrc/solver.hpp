@@ -1885,9 +1885,11 @@ __device__ __forceinline__ void solve_body(const SolveParams* __restrict__ Pg) {
 // nb = 1 (a grid barrier degenerates to a workgroup barrier), on its own slice
 // of the packed matrices and vectors; dense Q blocks use the streaming dense
 // product.  ||A|| comes from the same power iteration, per instance.
+// DENSE: the launch may hold instances with a dense or factored Q.
+template <bool DENSE>
 __device__ __forceinline__ void batch_solve(const BatchParams& BP) {
   __shared__ double lds[kWaves * 16];
-  __shared__ double svec[kDenseTile];
+  __shared__ double svec[DENSE ? kDenseTile : 1];
   const int idx = BP.order[blockIdx.x];
   __shared__ SolveParams Ps;
   // the partial sums of a phase go to LDS: with one workgroup per QP they
@@ -1938,10 +1940,12 @@ __device__ __forceinline__ void batch_solve(const BatchParams& BP) {
     S.norm_A = nrm;
   }
   __syncthreads();
-  if (P.Q.dense)
-    drive<true>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
-  else
+  if constexpr (DENSE) {
+    if (P.Q.dense) drive<true>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+    else drive<false>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+  } else {
     drive<false>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+  }
   if (B.tid == 0) BP.st[idx] = C.S;
 }
 
