@@ -507,44 +507,40 @@ __device__ PDHCG_PHASE void phase_cg_spmv(const SolveParams& P, Block B, const V
   }
   const WgPart& pt = P.w_cg;
   double s[1] = {0.0};
-  using T = std::conditional_t<sizeof(V) == 4, float, double>;  // gathered t: FP32 with FP32 values
-  if (P.lr_d) {  // low-rank Q: (P t)_i with t = P' p gathered, then + (d_i + 1/tau) p_i
-    const T* tv;
-    if constexpr (sizeof(V) == 4) tv = (const T*)P.lr_pt32; else tv = (const T*)P.lr_pt;
-    const GatherVec<T> gt{tv};
-    auto epi = [&](int i, double pt_i) {
-      const double pi = first ? P.r[i] : P.r[i] + beta * pprev[i];
-      const double qi = pt_i + (gld(P.lr_d + i) + inv_tau) * pi;
-      pcur[i] = pi;
-      P.q[i] = qi;
-      s[0] += pi * qi;
-    };
-    part_rows(pt, P.Q.rowptr, P.Q.col, qval, gt, epi);
-    for (int t = pt.l0; t < pt.l1; ++t) {
-      const int i = pt.long_rows[t];
-      double v[1] = {row_partial(P.Q.col, qval, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, gt)};
-      double dummy[1] = {0.0};
-      block_reduce<1, 0>(v, dummy, lds);
-      if (B.tid == 0) epi(i, v[0]);
-    }
-    double dummy[1] = {0.0};
-    store_partials<1, 0>(s, dummy, [](int) { return S_PQ; }, P.part, B.nb, B.b, lds);
-    return;
-  }
-  auto epi = [&](int i, double qp) {
-    const double pi = first ? P.r[i] : P.r[i] + beta * pprev[i];
-    const double qi = qp + pi * inv_tau;
-    pcur[i] = pi;
-    P.q[i] = qi;
+  const double *const rp = uni(P.r), *const pp = uni(pprev), *const lrd = uni(P.lr_d);
+  double *const pc = uni(pcur), *const q = uni(P.q);
+  const MemRows<V> mq{uni(P.Q.rowptr), uni(P.Q.col), uni(qval)};
+  // the owned rows' inputs (p_prev is always a valid buffer, not used when
+  // first is set), with the diagonal that the product leaves out: I / tau, and d
+  // of a low-rank Q = P P' + diag(d)
+  struct Row {
+    double r, p, d;
+  };
+  auto pre = [&](int ra, int i) {
+    return Row{gld_at(rp + ra, i), gld_at(pp + ra, i), lrd ? gld_at(lrd + ra, i) : 0.0};
+  };
+  auto epi = [&](int i, double qp, const Row& rw) {
+    const double pi = first ? rw.r : rw.r + beta * rw.p;
+    const double qi = lrd ? qp + (rw.d + inv_tau) * pi : qp + pi * inv_tau;
+    gst(pc + i, pi);
+    gst(q + i, qi);
     s[0] += pi * qi;
   };
-  part_rows(pt, P.Q.rowptr, P.Q.col, qval, gp, epi);
-  for (int t = pt.l0; t < pt.l1; ++t) {
-    const int i = pt.long_rows[t];
-    double v[1] = {row_partial(P.Q.col, qval, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, gp)};
-    double dummy[1] = {0.0};
-    block_reduce<1, 0>(v, dummy, lds);
-    if (B.tid == 0) epi(i, v[0]);
+  auto rows = [&](const auto& g) {
+    part_rows(pt, mq, g, pre, epi);
+    for (int t = pt.l0; t < pt.l1; ++t) {
+      const int i = pt.long_rows[t];
+      double v[1] = {row_partial(P.Q.col, qval, P.Q.rowptr[i], P.Q.rowptr[i + 1], B.tid, kBlock, g)};
+      double dummy[1] = {0.0};
+      block_reduce<1, 0>(v, dummy, lds);
+      if (B.tid == 0) epi(i, v[0], pre(i, 0));
+    }
+  };
+  if (lrd) {  // (P t)_i with t = P' p gathered (FP32 with FP32 values)
+    if constexpr (sizeof(V) == 4) rows(GatherVec<float>{uni((const float*)P.lr_pt32)});
+    else rows(GatherVec<double>{uni((const double*)P.lr_pt)});
+  } else {
+    rows(gp);
   }
   double dummy[1] = {0.0};
   store_partials<1, 0>(s, dummy, [](int) { return S_PQ; }, P.part, B.nb, B.b, lds);
