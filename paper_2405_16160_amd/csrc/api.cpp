@@ -5,10 +5,12 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cstdio>
 #include <limits>
 #include <map>
+#include <queue>
 #include <tuple>
 #include <string>
 #include <vector>
@@ -1215,6 +1217,100 @@ void batch_parts(const int64_t* qrp, bool dense, int64_t n, int64_t m, const int
   if (dense) g[0] = pow2_ceil(m ? (double)T.rowptr[n] / (double)n : 1.0);
 }
 
+// The four partitions of an instance for a team of nb workgroups, appended to
+// `out`: where each list starts
+struct TeamPart {
+  int64_t bounds, long_ptr, long_rows, tile_ptr, tiles;
+  int32_t group;
+};
+void team_parts(const int64_t* qrp, bool dense, int64_t n, int64_t m, const int64_t* arows, const HostCsr& T, int nb,
+                std::vector<int32_t>& out, TeamPart at[4]) {
+  const int64_t* q = dense ? nullptr : qrp;
+  const int64_t* trp = m ? T.rowptr.data() : nullptr;
+  const HostPart ps[4] = {build_part(n, nb, q, trp, 0, kBatchBlock), build_part(n, nb, q, nullptr, 0, kBatchBlock),
+                          build_part(m, nb, m ? arows : nullptr, nullptr, 0, kBatchBlock),
+                          build_part(n, nb, trp, nullptr, 0, kBatchBlock)};
+  for (int k = 0; k < 4; ++k) {
+    auto add = [&](const std::vector<int32_t>& v) {
+      const int64_t o = (int64_t)out.size();
+      out.insert(out.end(), v.begin(), v.end());
+      return o;
+    };
+    at[k] = TeamPart{add(ps[k].bounds), add(ps[k].long_ptr), add(ps[k].long_rows), add(ps[k].tile_ptr),
+                     add(ps[k].tiles), ps[k].group};
+  }
+}
+
+// Team sizes of a batch of 256-thread workgroups, by the estimated time of an
+// iteration.  One workgroup takes about 12 us and 0.9 ns per entry of the four
+// sparse passes, 5 ns per row of them and 1/64 ns per byte of the dense ones (a
+// CU reads no more than 64 B/ns from beyond its L2 slice): measured 93, 43 and
+// 22 us for portfolio QPs of n = 2000, 1000 and 300 (FP32 factor), 192 us for the
+// MPC QP of n = 1500, m = 5000.  A team of T divides all but a fixed part, which
+// its four or five barriers raise to 18 us.  Workgroups that share a CU slow one
+// another, by 1.4 when the card is full.  Candidates: every instance that takes
+// longer than some limit gets the smallest team that stays below it; the one whose
+// schedule (teams first, the others from the queue, largest first) ends first by
+// this model is taken, if it ends 5 % before the one without teams.  So a batch of
+// equal instances that fills the card stays without, and one that a few large
+// instances would hold up, or that leaves the card empty, is spread over it.
+// 100 iterations of 60 portfolio QPs, n <= 1500: 8.7 ms without teams, 4.4 with;
+// of 500, n <= 2000: 15.3, 10.1; 16 MPC QPs of T = 30 to 1e-4: 70, 21; 100 of
+// T = 50: 128, 49; 600 of them: 172 without, 212 with teams of two for half.
+constexpr int kMaxTeam = 8;  // (one QP of n = 2000: 4.3 ms with 8, 4.4 with 16)
+constexpr int kTeamRows = 64;  // rows per workgroup of a team, at least
+std::vector<int32_t> team_sizes(const std::vector<double>& work_us, const std::vector<int32_t>& rows, int resident,
+                                int cus) {
+  const int count = (int)work_us.size();
+  std::vector<int32_t> best(count, 1);
+  if (count == 0 || count > 8 * resident) return best;  // (a mean share far above any instance)
+  auto cost = [&](int i, int t) { return t == 1 ? 12.0 + work_us[i] : 18.0 + work_us[i] / t; };
+  std::vector<int> by_cost(count);
+  for (int i = 0; i < count; ++i) by_cost[i] = i;
+  std::stable_sort(by_cost.begin(), by_cost.end(), [&](int a, int b) { return work_us[a] > work_us[b]; });
+  auto ends = [&](const std::vector<int32_t>& T) {
+    int64_t wgs = 0;
+    for (int t : T) wgs += t;
+    const int slots = (int)std::min<int64_t>(wgs, resident);
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    double end = 0.0;
+    for (int i : by_cost)
+      if (T[i] > 1)
+        for (int r = 0; r < T[i]; ++r) free_at.push(cost(i, T[i]));
+    while ((int)free_at.size() < slots) free_at.push(0.0);
+    for (int i : by_cost) {
+      double e = cost(i, T[i]);
+      if (T[i] == 1) {
+        e += free_at.top();
+        free_at.pop();
+        free_at.push(e);
+      }
+      end = std::max(end, e);
+    }
+    return end * (1.0 + 0.4 * std::max(0.0, (double)(slots - cus) / std::max(1, resident - cus)));
+  };
+  double best_end = 0.95 * ends(best);
+  for (double limit = cost(by_cost[0], 1) / 1.2; limit > 20.0; limit /= 1.2) {
+    std::vector<int32_t> T(count, 1);
+    int64_t wgs = 0;
+    for (int i : by_cost) {
+      if (cost(i, 1) <= limit) break;
+      int t = 1;
+      while (t < kMaxTeam && rows[i] >= 2 * t * kTeamRows && cost(i, t) > limit) t <<= 1;
+      T[i] = cost(i, t) < cost(i, 1) ? t : 1;
+      if (T[i] > 1) wgs += T[i];
+    }
+    // (team workgroups are dealt out to the XCDs, at most one team unevenly)
+    if (wgs > resident - 8 * kMaxTeam) break;
+    const double e = ends(T);
+    if (e < best_end) {
+      best_end = e;
+      best = T;
+    }
+  }
+  return best;
+}
+
 // Device buffers of a batch: allocated with hipMalloc (and freed with the
 // batch), or, with an arena, carved from that region (the static scratch of
 // the allocation-free entry point: nothing is allocated or freed).
@@ -1278,6 +1374,11 @@ struct pdhcg_batch {
   double *x = nullptr, *y = nullptr;    // packed iterates (of the scaled problems when preconditioned)
   double *xo = nullptr, *yo = nullptr;  // returned points of the callers' problems
   BatchParams bp{};
+  int32_t* d_team_order = nullptr;   // the order with the team instances first
+  BatchTask* d_tasks = nullptr;
+  uint64_t* d_bars = nullptr;
+  uint32_t* d_queue = nullptr;
+  int32_t team_wgs = 0, nteams = 0, team_grid = 0;  // (no teams: nteams = 0)
   hipEvent_t e0 = nullptr, e1 = nullptr;
   double setup_s = 0.0;
   ~pdhcg_batch() {
@@ -1332,7 +1433,7 @@ int host_csr(const pdhcg_csr& M, std::vector<int64_t>& rp, std::vector<int32_t>&
 int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, const pdhcg_lowrank* Ls_in,
                       const pdhcg_csr* As_in, const double* const* bs_in, const double* const* cs_in,
                       int32_t vec_on_device, const pdhcg_settings* s, void* hip_stream, bool tunable,
-                      char* arena = nullptr, size_t arena_bytes = 0) {
+                      char* arena = nullptr, size_t arena_bytes = 0, bool may_share = true) {
   const double t0 = now_s();
   int rc;
   if (!out) return fail(PDHCG_ERR_INVALID_ARGUMENT, "null handle pointer");
@@ -1551,6 +1652,43 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
     return wa > wb;
   });
 
+  // ---- teams of workgroups for the instances that would hold the batch up
+  const bool adaptive = s->step_rule == 1;
+  bool any_dense = false;
+  for (int i = 0; i < count; ++i) any_dense |= inst[i].dense != 0;
+  h->any_dense = any_dense;
+  std::vector<int32_t> team(count, 1), team_of(count, -1), team_inst;
+  std::vector<std::array<TeamPart, 4>> team_part;
+  std::vector<int32_t> team_order;
+  int resident = 0, cus = 0;
+  // (the dense products of the adaptive step's trial have one workgroup)
+  if (may_share && !(adaptive && any_dense) && batch_resident(any_dense, &resident, &cus) == hipSuccess && resident > 0) {
+    std::vector<double> work(count);
+    std::vector<int32_t> rows(count);
+    for (int i = 0; i < count; ++i) {
+      const BatchInst& I = inst[i];
+      const double bytes = mixed ? 4.0 : 8.0, n = I.n, k = I.q_rank;
+      const double q = I.dense == 1 ? n * n * bytes / 64e3 : I.dense == 2 ? 2.0 * n * k * bytes / 64e3
+                                                                          : 2.0 * (double)Qs[i].nnz * 0.9e-3;
+      work[i] = q + 2.0 * (double)As[i].nnz * 0.9e-3 + 5e-3 * (n + I.m);
+      rows[i] = I.n;
+    }
+    team = team_sizes(work, rows, resident, cus);
+    for (int pass = 0; pass < 2; ++pass)
+      for (int i : order)
+        if ((team[i] > 1) == (pass == 0)) team_order.push_back(i);
+    for (int i : team_order) {
+      if (team[i] == 1) break;
+      team_of[i] = (int32_t)team_inst.size();
+      team_inst.push_back(i);
+      team_part.emplace_back();
+      team_parts(Ls ? nullptr : Qs[q_first[i]].rowptr, inst[i].dense != 0, inst[i].n, inst[i].m, As[i].rowptr,
+                 At[a_first[i]], team[i], parts, team_part.back().data());
+    }
+  }
+  const int nteams = (int)team_inst.size();
+  h->nteams = nteams;
+
   // ---- device buffers
   DevBuf& D = h->D;
   int32_t *d_rp, *d_col, *d_parts;
@@ -1568,7 +1706,7 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
   // values past the last matrix)
   if (mixed && (rc = D.alloc(&d_val32, nz_tot + 4))) return bail(rc);
   if ((rc = D.alloc(&d_parts, (int64_t)parts.size()))) return bail(rc);
-  if ((rc = D.alloc(&h->d_params, (int64_t)count * nsizes))) return bail(rc);
+  if ((rc = D.alloc(&h->d_params, (int64_t)count * nsizes + nteams))) return bail(rc);
   if ((rc = D.alloc(&h->d_st, count))) return bail(rc);
   if ((rc = D.alloc(&h->d_t0, 1))) return bail(rc);
   if ((rc = D.alloc(&h->d_given, count))) return bail(rc);
@@ -1576,10 +1714,6 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
   if ((rc = D.alloc(&d_c, vn_tot))) return bail(rc);
   if ((rc = D.alloc(&d_part, (int64_t)count * NSLOT))) return bail(rc);
   if ((rc = D.alloc(&h->d_order, count))) return bail(rc);
-  const bool adaptive = s->step_rule == 1;
-  bool any_dense = false;
-  for (int i = 0; i < count; ++i) any_dense |= inst[i].dense != 0;
-  h->any_dense = any_dense;
   for (int k = 0; k < 10; ++k) {
     nv[k] = nullptr;
     if ((k == 7 && !adaptive) || (k == 8 && !Ls) || (k == 9 && (adaptive || !any_dense))) continue;
@@ -1686,7 +1820,7 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
       return bail(fail(PDHCG_ERR_HIP, "preconditioning kernels failed to launch"));
   }
   // one parameter block per QP, all pointers resolved against the packed arrays
-  std::vector<SolveParams> hp((size_t)count * nsizes);
+  std::vector<SolveParams> hp((size_t)count * nsizes + nteams);
   for (int i = 0; i < count; ++i) {
     const BatchInst& I = inst[i];
     SolveParams& P = hp[i];
@@ -1756,6 +1890,58 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
       P.pm = part(2);
       P.pt = part(3);
     }
+  if (nteams > 0) {
+    // the members of a team on one XCD, where the dispatcher deals workgroups out
+    // to the XCDs in turn: its barrier and its matrix then stay in that L2
+    constexpr int kXcds = 8;
+    std::vector<BatchTask> tasks;
+    std::array<int, kXcds> fill{};
+    int64_t psum = 0, tsum = 0;
+    double *d_tpart = nullptr, *d_tlr = nullptr;
+    for (int t = 0; t < nteams; ++t) {
+      const int i = team_inst[t];
+      psum += (int64_t)team[i] * NSLOT;
+      tsum += (int64_t)team[i] * inst[i].q_rank;
+    }
+    if ((rc = D.alloc(&d_tpart, psum)) || (rc = D.alloc(&d_tlr, tsum)) ||
+        (rc = D.alloc(&h->d_bars, (int64_t)nteams * kBarWords)) || (rc = D.alloc(&h->d_queue, 1)) ||
+        (rc = D.alloc(&h->d_team_order, count)))
+      return bail(rc);
+    psum = tsum = 0;
+    for (int t = 0; t < nteams; ++t) {
+      const int i = team_inst[t], T = team[i], slot = count * nsizes + t;
+      SolveParams& P = hp[slot];
+      P = hp[i];
+      auto part = [&](int k) {
+        const TeamPart& a = team_part[t][k];
+        return Part{d_parts + a.bounds, d_parts + a.long_ptr, d_parts + a.long_rows, d_parts + a.tile_ptr,
+                    d_parts + a.tiles, a.group};
+      };
+      P.pn1 = part(0);
+      P.pcg = part(1);
+      P.pm = part(2);
+      P.pt = part(3);
+      const int x = (int)(std::min_element(fill.begin(), fill.end()) - fill.begin());
+      for (int r = 0; r < T; ++r) {
+        const size_t w = (size_t)x + kXcds * (size_t)(fill[x] + r);
+        if (tasks.size() <= w) tasks.resize(w + 1, BatchTask{0, 0, 0, 0, nullptr, nullptr, nullptr});
+        tasks[w] = BatchTask{i, slot, r, T, h->d_bars + (int64_t)t * kBarWords, d_tpart + psum, d_tlr + tsum};
+      }
+      fill[x] += T;
+      psum += (int64_t)T * NSLOT;
+      tsum += (int64_t)T * inst[i].q_rank;
+    }
+    h->team_wgs = (int32_t)tasks.size();
+    if (h->team_wgs > resident) {
+      h->nteams = 0;  // (uneven teams that fill one XCD's share: solved without)
+    } else {
+      h->team_grid = std::min(resident, h->team_wgs + (count - nteams));
+      if ((rc = D.alloc(&h->d_tasks, h->team_wgs))) return bail(rc);
+      if ((rc = up(h->d_tasks, tasks.data(), sizeof(BatchTask) * tasks.size()))) return bail(rc);
+      if ((rc = up(h->d_team_order, team_order.data(), sizeof(int32_t) * count))) return bail(rc);
+      if (hipStreamSynchronize(stream) != hipSuccess) return bail(fail(PDHCG_ERR_HIP, "batch upload failed"));
+    }
+  }
   if ((rc = up(h->d_params, hp.data(), sizeof(SolveParams) * hp.size()))) return bail(rc);
   if (mixed && launch_to_f32(d_val, d_val32, nz_tot, stream) != hipSuccess)
     return bail(fail(PDHCG_ERR_HIP, "FP32 conversion failed to launch"));
@@ -1776,6 +1962,7 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
   bp.mixed = mixed ? 1 : 0;
   bp.given = h->d_given;
   bp.warm_fallback = s->warm_fallback;
+  bp.count = count;
   h->setup_s = now_s() - t0;
   *out = h;
   return 0;
@@ -1784,13 +1971,24 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
 namespace {
 
 // The batch's start stamp and its one launch at the handle's workgroup size
-// (the parameter blocks of that size's partitions)
-hipError_t launch_batch(pdhcg_batch* h, hipStream_t stream) {
+// (the parameter blocks of that size's partitions), with the batch's teams if it
+// has any and they are wanted
+hipError_t launch_batch(pdhcg_batch* h, bool teams, hipStream_t stream) {
   BatchParams bp = h->bp;
   const int z = h->threads == kBatchSizes[1] ? 1 : 0;
+  teams = teams && z == 0 && h->nteams > 0;
   bp.params = h->d_params + (size_t)z * h->count;
-  hipError_t e = launch_batch_clock(bp.t0, stream);
+  if (teams) {
+    bp.order = h->d_team_order;
+    bp.tasks = h->d_tasks;
+    bp.team_wgs = h->team_wgs;
+    bp.queue = h->d_queue;
+  }
+  hipError_t e = teams ? launch_batch_clock(bp.t0, h->d_bars, (int64_t)h->nteams * kBarWords, h->d_queue,
+                                            (uint32_t)h->nteams, stream)
+                       : launch_batch_clock(bp.t0, nullptr, 0, nullptr, 0, stream);
   if (e != hipSuccess) return e;
+  if (teams) return launch_batch_teams(h->any_dense, bp, h->team_grid, stream);
   if (z) return launch_batch_512(bp, h->count, stream);
   return h->any_dense ? launch_batch_256(bp, h->count, stream) : launch_batch_sparse(bp, h->count, stream);
 }
@@ -1817,23 +2015,32 @@ int batch_solve_impl(pdhcg_batch* h, const double* x0, const double* y0, bool in
     if (y0) HIPX(launch_diag(h->d_y0, h->d_d1, h->vm_tot, 1, h->d_y0, stream));
   }
   HIPX(hipMemcpyAsync(h->d_given, g.data(), (size_t)count, hipMemcpyHostToDevice, stream));
-  if (h->e0) HIPX(hipEventRecord(h->e0, stream));
-  HIPX(launch_batch(h, stream));
-  if (h->e1) HIPX(hipEventRecord(h->e1, stream));
   const double* xr = h->x;
   const double* yr = h->y;
-  if (h->pre) {  // x = D2 x~, y = D1 y~
-    HIPX(launch_diag(h->x, h->d_d2, h->vn_tot, 0, h->xo, stream));
-    HIPX(launch_diag(h->y, h->d_d1, h->vm_tot, 0, h->yo, stream));
+  if (h->pre) {
     xr = h->xo;
     yr = h->yo;
   }
   const hipMemcpyKind out_kind = out_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   std::vector<SolverState> st(count);
-  HIPX(hipMemcpyAsync(st.data(), h->d_st, sizeof(SolverState) * count, hipMemcpyDeviceToHost, stream));
-  HIPX(hipMemcpyAsync(x_out, xr, sizeof(double) * h->vn_tot, out_kind, stream));
-  if (h->vm_tot) HIPX(hipMemcpyAsync(y_out, yr, sizeof(double) * h->vm_tot, out_kind, stream));
-  HIPX(hipStreamSynchronize(stream));
+  for (bool teams = true;; teams = false) {
+    if (h->e0) HIPX(hipEventRecord(h->e0, stream));
+    HIPX(launch_batch(h, teams, stream));
+    if (h->e1) HIPX(hipEventRecord(h->e1, stream));
+    if (h->pre) {  // x = D2 x~, y = D1 y~
+      HIPX(launch_diag(h->x, h->d_d2, h->vn_tot, 0, h->xo, stream));
+      HIPX(launch_diag(h->y, h->d_d1, h->vm_tot, 0, h->yo, stream));
+    }
+    HIPX(hipMemcpyAsync(st.data(), h->d_st, sizeof(SolverState) * count, hipMemcpyDeviceToHost, stream));
+    HIPX(hipMemcpyAsync(x_out, xr, sizeof(double) * h->vn_tot, out_kind, stream));
+    if (h->vm_tot) HIPX(hipMemcpyAsync(y_out, yr, sizeof(double) * h->vm_tot, out_kind, stream));
+    HIPX(hipStreamSynchronize(stream));
+    // a team's barrier timed out (its workgroups were kept from running together
+    // by other work on the card): once more, a workgroup per instance
+    const bool failed = std::any_of(st.begin(), st.end(), [](const SolverState& S) { return S.done < 0; });
+    if (!failed) break;
+    if (!teams) return fail(PDHCG_ERR_HIP, "the batched solve kernel failed");
+  }
   const double t_solve = now_s() - t0;
   float ms = (float)(t_solve * 1e3);
   if (h->e0) HIPX(hipEventElapsedTime(&ms, h->e0, h->e1));
@@ -1875,6 +2082,9 @@ int solve_batch_once(int32_t count, const pdhcg_csr* Qs, const pdhcg_lowrank* Ls
   }
   pdhcg_batch* h = nullptr;
   int rc = batch_create_impl(&h, count, Qs, Ls, As, bs, cs, 0, s, hip_stream, false, arena, arena_bytes);
+  // a batch that fits the region only without the teams' buffers goes without teams
+  if (rc == PDHCG_ERR_INVALID_ARGUMENT && arena)
+    rc = batch_create_impl(&h, count, Qs, Ls, As, bs, cs, 0, s, hip_stream, false, arena, arena_bytes, false);
   if (rc) return rc;
   std::vector<double> X0, Y0, X((size_t)h->vn_tot), Y((size_t)std::max<int64_t>(h->vm_tot, 1));
   std::vector<uint8_t> given(count, 0);
@@ -1949,7 +2159,7 @@ extern "C" int pdhcg_batch_autotune(pdhcg_batch* h, int32_t reps, int32_t* threa
     for (int r = 0; r < reps; ++r) {  // a cold solve of every instance; only the launch is timed
       HIPX(hipMemcpyAsync(h->d_given, cold.data(), cold.size(), hipMemcpyHostToDevice, h->stream));
       HIPX(hipEventRecord(h->e0, h->stream));
-      HIPX(launch_batch(h, h->stream));
+      HIPX(launch_batch(h, true, h->stream));
       HIPX(hipEventRecord(h->e1, h->stream));
       HIPX(hipStreamSynchronize(h->stream));
       float ms = 0.0f;

@@ -250,10 +250,23 @@ struct PowerParams {
   int32_t iters;
 };
 
+// One workgroup's place in a batch: instance, its parameter block (with the
+// partitions for `size` workgroups), number in the team and, for size > 1, the
+// team's barrier words, partial sums (NSLOT * size) and parts of F' v of a
+// factored Q (k * size).
+struct BatchTask {
+  int32_t inst, param, rank, size;
+  uint64_t* bar;
+  double* part;
+  double* lr_t;
+};
+
 // Batched solve: params[i] describes QP i (pointers into the packed device
-// arrays, its row partitions for one workgroup, its x0/y0); workgroup g
-// solves QP order[g].  Parameter blocks are written by the host before the
-// launch and only read by the kernel.
+// arrays, its row partitions for one workgroup, its x0/y0).  Without teams
+// workgroup g solves QP order[g]; with them, the first team_wgs workgroups have
+// tasks[g] (size 0: none) and the instances order[*queue ..) are taken one by
+// one.  Parameter blocks are written by the host before the launch and only read
+// by the kernel.
 struct BatchParams {
   const SolveParams* params;
   const int32_t* order;
@@ -266,6 +279,10 @@ struct BatchParams {
   // always point at the packed start buffers; without the bit the start is 0)
   const uint8_t* given;
   int32_t warm_fallback;  // compare a given start with (0, 0) (params' kkt_zero)
+  int32_t count;
+  const BatchTask* tasks;
+  int32_t team_wgs;
+  uint32_t* queue;
 };
 
 // records the message returned by pdhcg_last_error() and returns code
@@ -285,7 +302,13 @@ int solve_batch_in_region(int32_t count, const pdhcg_csr* Qs, const pdhcg_csr* A
 // the batched kernel with 256 (batch_kernels.hip; batch_kernels_sparse.hip when
 // every Q is sparse) or 512 threads per workgroup (batch_kernels_512.hip); the
 // clock kernel stamps the batch's start
-hipError_t launch_batch_clock(uint64_t* t0, hipStream_t s);
+// (and, for a launch with teams, clears their barrier words and sets the queue)
+hipError_t launch_batch_clock(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first,
+                              hipStream_t s);
+// the 256-thread kernels with teams (batch_kernels_team.hip): `grid` co-resident workgroups; batch_resident
+// is the largest such grid (and the number of CUs)
+hipError_t launch_batch_teams(bool dense, const BatchParams& p, int grid, hipStream_t s);
+hipError_t batch_resident(bool dense, int* grid, int* cus);
 hipError_t launch_batch_256(const BatchParams& p, int count, hipStream_t s);
 hipError_t launch_batch_sparse(const BatchParams& p, int count, hipStream_t s);
 hipError_t launch_batch_512(const BatchParams& p, int count, hipStream_t s);

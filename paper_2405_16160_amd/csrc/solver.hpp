@@ -63,7 +63,7 @@ __device__ __forceinline__ int trial_slot(int k) {
 // owned, row-major): out_c = sum_j M[j, c] v_j, which for a symmetric square M
 // is the product M v and for a tall factor F gives F' v.
 template <int K, typename V, typename Gen>
-__device__ __forceinline__ void dense_pass(const V* M, int nr, int nc, int i0, double* svec, Gen& gen,
+__device__ __forceinline__ void dense_pass(const V* M, int nr, int nc, int i0, bool first, double* svec, Gen& gen,
                                            double* acc) {
   constexpr int kJ = 8;  // rows per unrolled step
   int ic[K];
@@ -75,7 +75,7 @@ __device__ __forceinline__ void dense_pass(const V* M, int nr, int nc, int i0, d
   for (int j0 = 0; j0 < nr; j0 += kDenseTile) {
     const int jt = nr - j0 < kDenseTile ? nr - j0 : kDenseTile;
     __syncthreads();
-    for (int j = threadIdx.x; j < jt; j += kBlock) svec[j] = gen(j0 + j, i0 == 0);
+    for (int j = threadIdx.x; j < jt; j += kBlock) svec[j] = gen(j0 + j, first);
     __syncthreads();
     const V* base = M + (int64_t)j0 * nc;
     int j = 0;
@@ -110,7 +110,7 @@ __device__ __forceinline__ void dense_pass(const V* M, int nr, int nc, int i0, d
 // padding of the packed FP32 value array after the last matrix; those columns
 // are dropped.  A thread with no column below nc reads its row's start.
 template <typename Gen>
-__device__ __forceinline__ void dense_pass4(const float* M, int nr, int nc, int i0, double* svec, Gen& gen,
+__device__ __forceinline__ void dense_pass4(const float* M, int nr, int nc, int i0, bool first, double* svec, Gen& gen,
                                             double* acc) {
   constexpr int kJ = 16;  // rows per unrolled step
   const int c0 = i0 + 4 * (int)threadIdx.x;
@@ -120,7 +120,7 @@ __device__ __forceinline__ void dense_pass4(const float* M, int nr, int nc, int 
   for (int j0 = 0; j0 < nr; j0 += kDenseTile) {
     const int jt = nr - j0 < kDenseTile ? nr - j0 : kDenseTile;
     __syncthreads();
-    for (int j = threadIdx.x; j < jt; j += kBlock) svec[j] = gen(j0 + j, i0 == 0);
+    for (int j = threadIdx.x; j < jt; j += kBlock) svec[j] = gen(j0 + j, first);
     __syncthreads();
     const float* base = M + (int64_t)j0 * nc + cl;
     int j = 0;
@@ -148,35 +148,35 @@ __device__ __forceinline__ void dense_pass4(const float* M, int nr, int nc, int 
   }
 }
 
-// out_c = sum_j M[j, c] v_j for all c < nc, v_j = gen(j, first) (first: the
-// first column pass, where gen may store what it forms), epi(c, out_c)
+// out_c = sum_j M[j, c] v_j for the columns c0 <= c < c1 of nc, v_j = gen(j, first)
+// (first: the first column pass, where gen may store what it forms), epi(c, out_c)
 template <typename V, typename Gen, typename Epi>
-__device__ void rect_rows(const V* M, int nr, int nc, double* svec, Gen& gen, Epi& epi) {
+__device__ void rect_rows(const V* M, int nr, int nc, int c0, int c1, double* svec, Gen& gen, Epi& epi) {
   if constexpr (sizeof(V) == 4) {
-    for (int i0 = 0; i0 < nc; i0 += 4 * kBlock) {
+    for (int i0 = c0; i0 < c1; i0 += 4 * kBlock) {
       double acc[4];
-      dense_pass4(M, nr, nc, i0, svec, gen, acc);
+      dense_pass4(M, nr, nc, i0, i0 == c0, svec, gen, acc);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int i = i0 + 4 * (int)threadIdx.x + q;
-        if (i < nc) epi(i, acc[q]);
+        if (i < c1) epi(i, acc[q]);
       }
     }
     __syncthreads();
     return;
   }
-  for (int i0 = 0; i0 < nc; i0 += kBlock * kDenseRows) {
+  for (int i0 = c0; i0 < c1; i0 += kBlock * kDenseRows) {
     double acc[kDenseRows];
-    const int cols = nc - i0;
+    const int cols = c1 - i0;
     const int K = cols > 3 * kBlock ? 4 : (cols > 2 * kBlock ? 3 : (cols > kBlock ? 2 : 1));  // uniform
-    if (K == 4) dense_pass<4>(M, nr, nc, i0, svec, gen, acc);
-    else if (K == 3) dense_pass<3>(M, nr, nc, i0, svec, gen, acc);
-    else if (K == 2) dense_pass<2>(M, nr, nc, i0, svec, gen, acc);
-    else dense_pass<1>(M, nr, nc, i0, svec, gen, acc);
+    if (K == 4) dense_pass<4>(M, nr, nc, i0, i0 == c0, svec, gen, acc);
+    else if (K == 3) dense_pass<3>(M, nr, nc, i0, i0 == c0, svec, gen, acc);
+    else if (K == 2) dense_pass<2>(M, nr, nc, i0, i0 == c0, svec, gen, acc);
+    else dense_pass<1>(M, nr, nc, i0, i0 == c0, svec, gen, acc);
 #pragma unroll
     for (int k = 0; k < kDenseRows; ++k) {
       const int i = i0 + (int)threadIdx.x + k * kBlock;
-      if (k < K && i < nc) epi(i, acc[k]);
+      if (k < K && i < c1) epi(i, acc[k]);
     }
   }
   __syncthreads();
@@ -189,8 +189,8 @@ __device__ void rect_rows(const V* M, int nr, int nc, double* svec, Gen& gen, Ep
 // columns lane + 64 q (all waves busy, where one thread per column would
 // leave most of them idle); the waves' partial sums are added in LDS in a
 // fixed order.  red holds kWaves * 256 doubles.
-template <int Q4, typename V>
-__device__ void factor_tv(const V* F, int n, int k, const double* svec, double* red, double* t) {
+template <int Q4, typename V, typename Put>
+__device__ void factor_tv(const V* F, int n, int k, const double* svec, double* red, Put& put) {
   constexpr int kJ = 8;  // rows per unrolled step (per wave)
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   double acc[Q4];
@@ -225,7 +225,7 @@ __device__ void factor_tv(const V* F, int n, int k, const double* svec, double* 
   for (int c = tid; c < k; c += kBlock) {
     double sum = red[c];
     for (int ww = 1; ww < kWaves; ++ww) sum += red[ww * 256 + c];
-    t[c] = sum;
+    put(c, sum);
   }
   __syncthreads();
 }
@@ -235,7 +235,8 @@ __device__ void factor_tv(const V* F, int n, int k, const double* svec, double* 
 // step; each column adds its rows in the same order as factor_tv, so t is the
 // same.  A lane whose columns run past k reads up to three values beyond the
 // row (the next row, or F' after the last row); those are dropped.
-__device__ void factor_tv4(const float* F, int n, int k, const double* svec, double* red, double* t) {
+template <typename Put>
+__device__ void factor_tv4(const float* F, int n, int k, const double* svec, double* red, Put& put) {
   constexpr int kJ = 16;  // rows per unrolled step (per wave)
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const int c0 = 4 * lane;
@@ -267,68 +268,113 @@ __device__ void factor_tv4(const float* F, int n, int k, const double* svec, dou
   for (int c = tid; c < k; c += kBlock) {
     double sum = red[c];
     for (int ww = 1; ww < kWaves; ++ww) sum += red[ww * 256 + c];
-    t[c] = sum;
+    put(c, sum);
   }
   __syncthreads();
 }
 
-// Q v for a dense Q of one workgroup: full n x n rows (Q.dense = 1), or Q =
-// F F' + diag(d) from its factor (Q.dense = 2; Q.rank = k; the block holds F
+// out_c = sum_j M[j, c] v_j for all k <= 256 columns and n <= kDenseTile rows, v
+// staged from gen(j, true), put(c, out_c)
+template <typename V, typename Gen, typename Put>
+__device__ __forceinline__ void narrow_rows(const V* M, int n, int k, double* svec, Gen& gen, Put& put) {
+  __syncthreads();
+  for (int j = (int)threadIdx.x; j < n; j += kBlock) svec[j] = gen(j, true);
+  __syncthreads();
+  double* red = &tile_lds().prod[0][0];  // no tile is staged during a dense product
+  if constexpr (sizeof(V) == 4) factor_tv4(M, n, k, svec, red, put);
+  else if (k <= 64) factor_tv<1>(M, n, k, svec, red, put);
+  else if (k <= 128) factor_tv<2>(M, n, k, svec, red, put);
+  else if (k <= 192) factor_tv<3>(M, n, k, svec, red, put);
+  else factor_tv<4>(M, n, k, svec, red, put);
+}
+
+// t = F' v over the rows r0 <= j < r1 of a factored Q, v_j = gen(j, true), into
+// t (k values)
+template <typename V, typename Gen>
+__device__ __forceinline__ void factor_rows(const V* M, const DevMat& Q, int r0, int r1, double* svec, double* t,
+                                            Gen& gen) {
+  const int n = r1 - r0, k = Q.rank;
+  const V* const F = M + (int64_t)r0 * k;
+  auto row = [&](int j, bool first) { return gen(r0 + j, first); };
+  auto put_t = [&](int c, double s) { t[c] = s; };
+  if (n <= kDenseTile && k <= 256) narrow_rows(F, n, k, svec, row, put_t);
+  else rect_rows(F, n, k, 0, k, svec, row, put_t);  // (both end with a workgroup barrier: t visible)
+}
+
+// The rows r0 <= i < r1 of Q v for a dense Q: full n x n rows (Q.dense = 1), or
+// Q = F F' + diag(d) from its factor (Q.dense = 2; Q.rank = k; the block holds F
 // (n x k), F' (k x n) and d, row-major, at M): t = F' v into tscr (k), then
-// F t + d v, 2 n k values read instead of n^2.
+// F t + d v, 2 n k values read instead of n^2.  With several workgroups on the QP
+// (B.nb > 1), each has left its rows' part of t at tscr + k * its number before
+// (factor_part and a barrier), and the parts are added here.  gen stores what it
+// forms (first pass) for the own rows only.
 template <typename V, typename Gen, typename Epi>
-__device__ void dense_rows(const V* M, const DevMat& Q, double* svec, double* tscr, Gen gen, Epi epi) {
+__device__ void dense_rows(const V* M, const DevMat& Q, Block B, int r0, int r1, double* svec, double* tscr, Gen gen,
+                           Epi epi) {
   const int n = Q.nrows;
   if (Q.dense != 2) {
-    rect_rows(M, n, n, svec, gen, epi);
+    auto own = [&](int j, bool first) { return gen(j, first && j >= r0 && j < r1); };
+    rect_rows(M, n, n, r0, r1, svec, own, epi);
     return;
   }
   const int k = Q.rank;
   const V* Ft = M + (int64_t)n * k;
   const V* d = Ft + (int64_t)k * n;
-  if (n <= kDenseTile && k <= 256) {
-    __syncthreads();
-    for (int j = (int)threadIdx.x; j < n; j += kBlock) svec[j] = gen(j, true);
-    __syncthreads();
-    double* red = &tile_lds().prod[0][0];  // no tile is staged during a dense product
-    if constexpr (sizeof(V) == 4) factor_tv4(M, n, k, svec, red, tscr);
-    else if (k <= 64) factor_tv<1>(M, n, k, svec, red, tscr);
-    else if (k <= 128) factor_tv<2>(M, n, k, svec, red, tscr);
-    else if (k <= 192) factor_tv<3>(M, n, k, svec, red, tscr);
-    else factor_tv<4>(M, n, k, svec, red, tscr);
-  } else {
-    auto put_t = [&](int c, double s) { tscr[c] = s; };
-    rect_rows(M, n, k, svec, gen, put_t);  // (ends with a workgroup barrier: tscr visible)
-  }
-  auto get_t = [&](int c, bool) { return tscr[c]; };
+  if (B.nb == 1) factor_rows(M, Q, r0, r1, svec, tscr, gen);
+  auto get_t = [&](int c, bool) {
+    double t = tscr[c];
+    for (int w = 1; w < B.nb; ++w) t += tscr[(int64_t)w * k + c];
+    return t;
+  };
   auto fin = [&](int i, double s) { epi(i, s + (double)d[i] * gen(i, false)); };
-  rect_rows(Ft, k, n, svec, get_t, fin);
+  rect_rows(Ft, k, n, r0, r1, svec, get_t, fin);
 }
 
-// out = Q xv for a dense Q owned by one workgroup
-__device__ PDHCG_PHASE void dense_qx(const SolveParams& P, const double* xv, double* svec, double* out) {
-  dense_rows(P.Q.val, P.Q, svec, P.lr_t, [&](int j, bool) { return xv[j]; }, [&](int i, double v) { out[i] = v; });
+// what the dense products multiply: a vector, or the CG direction p = r + beta
+// p_prev, stored as it is formed
+struct DenseVec {
+  const double* v;
+  __device__ __forceinline__ double operator()(int j, bool) const { return v[j]; }
+};
+struct DenseDir {
+  const double* r;
+  const double* pp;
+  double* pc;
+  double beta;
+  int first;
+  __device__ __forceinline__ double operator()(int j, bool store) const {
+    const double pj = first ? r[j] : r[j] + beta * pp[j];
+    if (store) pc[j] = pj;
+    return pj;
+  }
+};
+
+// this workgroup's part of t = F' v, for a factored Q that several workgroups share
+template <typename V, typename Gen>
+__device__ PDHCG_PHASE void factor_part(const SolveParams& P, const WgPart& pt, Block B, const V* M, const Gen gen,
+                                        double* svec) {
+  factor_rows(M, P.Q, pt.r0, pt.r1, svec, P.lr_t + (int64_t)B.b * P.Q.rank, gen);
 }
 
-// CG product for a dense Q owned by one workgroup: stage p in LDS, stream Q
+// the rows of out = Q xv for a dense Q
+__device__ PDHCG_PHASE void dense_qx(const SolveParams& P, const WgPart& pt, Block B, const double* xv, double* svec,
+                                     double* out) {
+  dense_rows(P.Q.val, P.Q, B, pt.r0, pt.r1, svec, P.lr_t, DenseVec{xv}, [&](int i, double v) { out[i] = v; });
+}
+
+// CG product for a dense Q: stage p in LDS, stream Q
 template <typename V>
 __device__ PDHCG_PHASE void dense_cg_spmv(const SolveParams& P, Block B, const V* qd,
                                                         const double* pprev, double* pcur, double beta, int first,
                                                         double inv_tau, double* lds, double* svec) {
   double s[1] = {0.0}, dummy[1] = {0.0};
-  dense_rows(
-      qd, P.Q, svec, P.lr_t,
-      [&](int j, bool first_pass) {
-        const double pj = first ? P.r[j] : P.r[j] + beta * pprev[j];
-        if (first_pass) pcur[j] = pj;
-        return pj;
-      },
-      [&](int i, double qp) {
-        const double pi = first ? P.r[i] : P.r[i] + beta * pprev[i];
-        const double qi = qp + pi * inv_tau;
-        P.q[i] = qi;
-        s[0] += pi * qi;
-      });
+  dense_rows(qd, P.Q, B, P.w_cg.r0, P.w_cg.r1, svec, P.lr_t, DenseDir{P.r, pprev, pcur, beta, first},
+             [&](int i, double qp) {
+               const double pi = first ? P.r[i] : P.r[i] + beta * pprev[i];
+               const double qi = qp + pi * inv_tau;
+               P.q[i] = qi;
+               s[0] += pi * qi;
+             });
   store_partials<1, 0>(s, dummy, [](int) { return S_PQ; }, P.part, B.nb, B.b, lds);
 }
 
@@ -347,7 +393,7 @@ __device__ PDHCG_PHASE void phase_nside(const SolveParams& P, const WgPart& pt, 
   // dense Q (one workgroup per QP): Q xv first, into q or qx, unless qx is kept
   constexpr bool dense = DENSE;
   double* const qsrc = qmode == QX_INTO_Q ? P.q : P.qx;
-  if (dense && qmode != QX_KEPT) dense_qx(P, xv, svec, qsrc);
+  if (dense && qmode != QX_KEPT) dense_qx(P, pt, B, xv, svec, qsrc);
   const int G = pt.group;
   double s[3] = {0.0, 0.0, 0.0};   // g.g, x.Qx, c.x
   double mx[3] = {0.0, 0.0, 0.0};  // |g|, |Qx|, |A'y|
@@ -840,7 +886,8 @@ __device__ PDHCG_PHASE void phase_dual_trial(const SolveParams& P, Block B, cons
     sm[4] += dx * qd;
   };
   if constexpr (DENSE) {
-    dense_rows(P.Q.val, P.Q, svec, P.lr_t, [&](int j, bool) { return gld(P.x + j) - gld(P.x_prev + j); }, epi);
+    dense_rows(P.Q.val, P.Q, B, P.w_cg.r0, P.w_cg.r1, svec, P.lr_t,
+               [&](int j, bool) { return gld(P.x + j) - gld(P.x_prev + j); }, epi);
   } else {
     const WgPart& pt = P.w_cg;
     const GatherDiff g{P.x, P.x_prev};
@@ -1565,6 +1612,22 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
       }
       if (!(ok = gs.sync())) break;
     }
+    if constexpr (DENSE) {
+      // a factored Q of several workgroups: their parts of t = F' v first
+      const bool kept = op == OP_NSIDE && P.qx && !C.exact;
+      if (B.nb > 1 && P.Q.dense == 2 && !kept &&
+          (op == OP_NSIDE || op == OP_EVAL || op == OP_LIMIT_EVAL || op == OP_CG_SPMV)) {
+        if (op == OP_CG_SPMV) {
+          const int cur = C.cur;
+          const DenseDir dir{P.r, cur ? P.p0 : P.p1, cur ? P.p1 : P.p0, C.beta, C.first};
+          if (mixed) factor_part(P, P.w_cg, B, P.Q.val32, dir, svec);
+          else factor_part(P, P.w_cg, B, P.Q.val, dir, svec);
+        } else {
+          factor_part(P, P.w_n1, B, P.Q.val, DenseVec{op == OP_NSIDE ? P.x : P.xa}, svec);
+        }
+        if (!(ok = gs.sync())) break;
+      }
+    }
     switch (op) {
       case OP_AX_START:
       case OP_AX_ZERO:
@@ -1875,26 +1938,29 @@ __device__ __forceinline__ void solve_body(const SolveParams* __restrict__ Pg) {
 
 // -------------------------------------------------------------- batched solve
 
-// One workgroup per QP: workgroup g solves instance order[g] (the host sorts
-// instances by decreasing work, so the dispatcher hands out the largest
-// first).  Each workgroup runs the same loop as the cooperative kernel with
-// nb = 1 (a grid barrier degenerates to a workgroup barrier), on its own slice
-// of the packed matrices and vectors; dense Q blocks use the streaming dense
-// product.  ||A|| comes from the same power iteration, per instance.
-// DENSE: the launch may hold instances with a dense or factored Q.
-template <bool DENSE>
-__device__ __forceinline__ void batch_solve(const BatchParams& BP) {
+// One instance, by one workgroup (nb = 1: a grid barrier degenerates to a
+// workgroup barrier) or by a team of nb of them (b is this one's number; bar the
+// team's barrier words, part its partial sums, lr_t its parts of F' v): the same
+// loop as the cooperative kernel, on the instance's slice of the packed matrices
+// and vectors; dense Q blocks use the streaming dense product.  ||A|| comes from
+// the same power iteration, per instance.
+// DENSE: the launch may hold instances with a dense or factored Q.  TEAM: it may
+// hold teams; without, the one workgroup is known to the compiler, and the
+// barriers and reductions over workgroups are not in the code.
+template <bool DENSE, bool TEAM>
+__device__ __forceinline__ void batch_instance(const BatchParams& BP, const BatchTask& task) {
   __shared__ double lds[kWaves * 16];
   __shared__ double svec[DENSE ? kDenseTile : 1];
-  const int idx = BP.order[blockIdx.x];
+  const int idx = task.inst, nb = TEAM ? task.size : 1, rank = TEAM ? task.rank : 0;
   __shared__ SolveParams Ps;
-  // the partial sums of a phase go to LDS: with one workgroup per QP they
+  // the partial sums of a phase go to LDS when one workgroup has the QP: they
   // are read back only by the same workgroup, after a workgroup barrier
   __shared__ double part_lds[NSLOT];
-  load_params(Ps, BP.params + idx, 0);
-  fill_wg_part(Ps.w_lr, Ps.pt, 0);  // (a batch has no sparse low-rank Q: the share of A' for the power iteration)
+  load_params(Ps, BP.params + task.param, rank);
+  fill_wg_part(Ps.w_lr, Ps.pt, rank);  // (a batch has no sparse low-rank Q: the share of A' for the power iteration)
   if (threadIdx.x == 0) {  // this solve's partials, start point and warm-start fallback
-    Ps.part = part_lds;
+    Ps.part = nb > 1 ? task.part : part_lds;
+    if (nb > 1) Ps.lr_t = task.lr_t;
     const uint32_t gv = BP.given ? BP.given[idx] : 0u;
     if (!(gv & 1u)) Ps.x0 = nullptr;
     if (!(gv & 2u)) Ps.y0 = nullptr;
@@ -1902,25 +1968,27 @@ __device__ __forceinline__ void batch_solve(const BatchParams& BP) {
   }
   __syncthreads();
   const SolveParams& P = Ps;
-  Block B{0, 1, (int)threadIdx.x};
-  GridSync gs{nullptr, 1u, 0};
+  Block B{rank, nb, (int)threadIdx.x};
+  GridSync gs{TEAM ? task.bar : nullptr, (uint32_t)nb, 0};
+  bool ok = TEAM ? gs.init() : true;
   // start point (x0 or 0; y0 projected onto y >= 0, or 0)
-  for (int j = B.tid; j < P.n; j += kBlock) {
+  for (int j = B.b * kBlock + B.tid; j < P.n; j += nb * kBlock) {
     const double v = P.x0 ? P.x0[j] : 0.0;
     P.x[j] = v;
     P.xa[j] = v;
     P.x_anc[j] = v;
     if (BP.mixed) P.x32[j] = (float)v;
   }
-  for (int i = B.tid; i < P.m; i += kBlock) {
+  for (int i = B.b * kBlock + B.tid; i < P.m; i += nb * kBlock) {
     const double v = pos_part(P.y0 ? P.y0[i] : 0.0);
     P.y[i] = v;
     P.ya[i] = v;
     P.y_anc[i] = v;
   }
-  __syncthreads();
+  ok = ok && gs.sync();
   double nrm = 0.0;
-  if (P.m > 0) power_norm(P.A, P.At, P.p1, P.ax_avg, P.part, P.w_lr, P.w_m, BP.power_iters, B, gs, lds, &nrm);
+  if (ok && P.m > 0)
+    ok = power_norm(P.A, P.At, P.p1, P.ax_avg, P.part, P.w_lr, P.w_m, BP.power_iters, B, gs, lds, &nrm);
   __shared__ Ctl C;
   if (B.tid == 0) {
     SolverState& S = C.S;
@@ -1936,13 +2004,53 @@ __device__ __forceinline__ void batch_solve(const BatchParams& BP) {
     S.norm_A = nrm;
   }
   __syncthreads();
-  if constexpr (DENSE) {
-    if (P.Q.dense) drive<true>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
-    else drive<false>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
-  } else {
-    drive<false>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+  if (ok) {
+    if constexpr (DENSE) {
+      if (P.Q.dense) ok = drive<true>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+      else ok = drive<false>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+    } else {
+      ok = drive<false>(P, B, gs, C, P.nb_inf, P.nc_inf, lds, svec, INT64_MAX);
+    }
   }
-  if (B.tid == 0) BP.st[idx] = C.S;
+  if (B.b == 0 && B.tid == 0) {
+    if (!ok) C.S.done = -1;  // a team's barrier failed: the host solves the batch without teams
+    BP.st[idx] = C.S;
+  }
+}
+
+// Without teams: workgroup g solves instance order[g] (the host sorts the
+// instances by decreasing work, so the dispatcher hands out the largest first).
+template <bool DENSE>
+__device__ __forceinline__ void batch_solve(const BatchParams& BP) {
+  const int i = BP.order[blockIdx.x];
+  batch_instance<DENSE, false>(BP, BatchTask{i, i, 0, 1, nullptr, nullptr, nullptr});
+}
+
+// With teams, in a co-resident launch: the workgroups of the teams solve their
+// instance first, and then all take the other instances from a queue, again the
+// largest first.
+template <bool DENSE>
+__device__ __forceinline__ void batch_team_solve(const BatchParams& BP) {
+  const int g = (int)blockIdx.x;
+  __shared__ uint32_t next;
+  __shared__ BatchTask task;
+  bool team = g < BP.team_wgs && BP.tasks[g].size > 0;
+  for (;;) {
+    if (threadIdx.x == 0) {
+      if (team) {
+        task = BP.tasks[g];
+      } else {
+        next = PDHCG_ADD(BP.queue, 1u);
+        const int i = next < (uint32_t)BP.count ? BP.order[next] : 0;
+        task = BatchTask{i, i, 0, 1, nullptr, nullptr, nullptr};
+      }
+    }
+    __syncthreads();
+    if (!team && next >= (uint32_t)BP.count) return;
+    team = false;
+    batch_instance<DENSE, true>(BP, task);
+    __syncthreads();
+  }
 }
 
 // ||A||_2 by the power iteration on A'A, every workgroup taking its rows of
