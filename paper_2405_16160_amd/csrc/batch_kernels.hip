@@ -17,17 +17,19 @@ namespace pdhcg {
 // launch size alone the compiler takes the whole register file.
 __global__ void __launch_bounds__(kSolveBlock) pdhcg_batch_kernel(BatchParams BP) { batch_solve<true>(BP); }
 
-__global__ void batch_clock_kernel(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first) {
+__global__ void batch_clock_kernel(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first,
+                                   double* norm) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) *t0 = wall_clock64();
   if (i == 0 && queue) *queue = first;
+  if (i == 0 && norm) *norm = -1.0;
   for (int64_t k = i; k < nbars; k += (int64_t)gridDim.x * blockDim.x) bars[k] = 0;
 }
 
 hipError_t launch_batch_clock(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first,
-                              hipStream_t s) {
+                              double* norm, hipStream_t s) {
   const int grid = nbars > 0 ? (int)((nbars + 255) / 256 < 256 ? (nbars + 255) / 256 : 256) : 1;
-  hipLaunchKernelGGL(batch_clock_kernel, dim3(grid), dim3(256), 0, s, t0, bars, nbars, queue, first);
+  hipLaunchKernelGGL(batch_clock_kernel, dim3(grid), dim3(256), 0, s, t0, bars, nbars, queue, first, norm);
   return hipGetLastError();
 }
 

@@ -279,6 +279,7 @@ struct BatchParams {
   // always point at the packed start buffers; without the bit the start is 0)
   const uint8_t* given;
   int32_t warm_fallback;  // compare a given start with (0, 0) (params' kkt_zero)
+  const double* norm;     // ||A||_2 where all members share A (negative: not formed), or null
   int32_t count;
   const BatchTask* tasks;
   int32_t team_wgs;
@@ -302,9 +303,10 @@ int solve_batch_in_region(int32_t count, const pdhcg_csr* Qs, const pdhcg_csr* A
 // the batched kernel with 256 (batch_kernels.hip; batch_kernels_sparse.hip when
 // every Q is sparse) or 512 threads per workgroup (batch_kernels_512.hip); the
 // clock kernel stamps the batch's start
-// (and, for a launch with teams, clears their barrier words and sets the queue)
+// (and clears the barrier words that the launch uses, sets the queue of one with
+// teams and marks the shared norm as not formed)
 hipError_t launch_batch_clock(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first,
-                              hipStream_t s);
+                              double* norm, hipStream_t s);
 // the 256-thread kernels with teams (batch_kernels_team.hip): `grid` co-resident workgroups; batch_resident
 // is the largest such grid (and the number of CUs)
 hipError_t launch_batch_teams(bool dense, const BatchParams& p, int grid, hipStream_t s);

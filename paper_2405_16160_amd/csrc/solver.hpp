@@ -1990,8 +1990,11 @@ __device__ __forceinline__ void batch_instance(const BatchParams& BP, const Batc
     P.y_anc[i] = v;
   }
   ok = ok && gs.sync();
-  double nrm = 0.0;
-  if (ok && P.m > 0)
+  // ||A||: formed for the whole batch where its members share A, unless that launch
+  // failed; else here
+  double nrm = BP.norm ? *BP.norm : -1.0;
+  if (nrm < 0.0) nrm = 0.0;
+  if (ok && P.m > 0 && !(BP.norm && *BP.norm >= 0.0))
     ok = power_norm(P.A, P.At, P.p1, P.ax_avg, P.part, P.w_lr, P.w_m, BP.power_iters, B, gs, lds, &nrm);
   __shared__ Ctl C;
   if (B.tid == 0) {

@@ -39,7 +39,7 @@ def batch_of(name):
         qps = [I.portfolio_qp(i, n=n) for i, n in enumerate((640, 512))]
         empty = lambda n: I.CSR(0, n, np.zeros(1, np.int64), np.zeros(0, np.int32), np.zeros(0))
         return [I.QP(q.Q, empty(q.n), np.zeros(0), q.c) for q in qps], None
-    else:                      # members that share Q and A
+    else:                      # members that share Q and A (and one launch for ||A||)
         fam = I.mpc_family(T=30, nx=12, nu=5)
         rng = np.random.default_rng(3)
         return [I.QP(fam.Q, fam.A, fam.b_for(0.1 * rng.standard_normal(fam.nx)), fam.c) for _ in range(7)], None
@@ -82,3 +82,20 @@ def test_team_against_oracle():
         assert O.kkt(qp, x, y)["rel_kkt"] <= 1e-6 * (1 + 1e-6)
         assert np.linalg.norm(x - ref.x) <= 1e-4 * np.linalg.norm(ref.x)
     b.close()
+
+
+def test_shared_norm():
+    """||A|| formed once for a family equals the oracle's and every member's own
+    (100 steps of the power iteration, sums of at most 2000 terms: 1e-12)."""
+    qps, _ = batch_of("family")
+    s = pdhcg.Settings(tol_rel_kkt=1e-4, max_iters=3)
+    shared = pdhcg.Batch(qps, s)
+    rs = shared.solve()[2]
+    A = qps[0].A
+    copy = I.CSR(A.nrows, A.ncols, A.rowptr.copy(), A.col.copy(), A.val.copy())
+    own = pdhcg.Batch(qps[:1] + [I.QP(qps[1].Q, copy, qps[1].b, qps[1].c)], s)   # two matrices: no sharing
+    want = O.opnorm(A)
+    for r in rs + own.solve()[2]:
+        assert r["norm_A"] == pytest.approx(want, rel=1e-12)
+    shared.close()
+    own.close()
