@@ -6,7 +6,8 @@
 // kStreamRows rows, or a single row longer than kStreamNnz (a long tile),
 // cut on the host: tiles[4 t .. 4 t + 3] = first row, end row, first entry,
 // end entry.  A regular tile stages val * x[col] for all its entries in LDS
-// with one burst of loads (unconditional, indices clamped into the tile),
+// with one burst of loads (indices clamped into the tile, steps that it does not
+// have skipped),
 // then sums each row with a group of lanes sized to the tile's row count
 // (data-parallel-primitive lane moves, no LDS shuffles; a row far longer
 // than its group is summed by a whole wave instead).  A long tile is
@@ -92,27 +93,36 @@ __global__ void __launch_bounds__(kStreamBlock) spmv_stream_kernel(const int32_t
   if (tid == 0) nwide = 0;
   int rv[kStreamRowLoads];
 #pragma unroll
-  for (int u = 0; u < kStreamRowLoads; ++u) rv[u] = gld(rowptr + r0 + min(u * kStreamBlock + tid, nr));
+  for (int u = 0; u < kStreamRowLoads; ++u) {
+    if (u * kStreamBlock > nr) break;
+    rv[u] = gld(rowptr + r0 + min(u * kStreamBlock + tid, nr));
+  }
   if (ne > 0) {
     int c[kStreamUnroll];
     V v[kStreamUnroll];
 #pragma unroll
     for (int u = 0; u < kStreamUnroll; ++u) {
+      if (u * kStreamBlock >= ne) break;
       const int k = min(u * kStreamBlock + tid, ne - 1);
       c[u] = gld_nt(col + e0 + k);
       v[u] = gld_nt(val + e0 + k);
     }
     double g[kStreamUnroll];
 #pragma unroll
-    for (int u = 0; u < kStreamUnroll; ++u) g[u] = (double)gld(x + c[u]);
+    for (int u = 0; u < kStreamUnroll; ++u) {
+      if (u * kStreamBlock >= ne) break;
+      g[u] = (double)gld(x + c[u]);
+    }
 #pragma unroll
     for (int u = 0; u < kStreamUnroll; ++u) {
+      if (u * kStreamBlock >= ne) break;
       const int k = u * kStreamBlock + tid;
       if (k < ne) prod[k] = (double)v[u] * g[u];
     }
   }
 #pragma unroll
   for (int u = 0; u < kStreamRowLoads; ++u) {
+    if (u * kStreamBlock > nr) break;
     const int i = u * kStreamBlock + tid;
     if (i <= nr) rp[i] = rv[u] - e0;
   }

@@ -63,3 +63,25 @@ def test_row_lengths(name, threads, precision):
         x, y = x.cpu().numpy(), y.cpu().numpy()
         assert np.linalg.norm(x - ref.x) <= tol * np.linalg.norm(ref.x)
         assert np.linalg.norm(y - ref.y) <= tol * max(np.linalg.norm(ref.y), np.linalg.norm(ref.x))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("lens", [[255, 1], [256], [257, 0, 3], [1] * 129, [5] * 700, [2047, 1, 2048, 2049], [0, 0]])
+def test_product_tiles(lens, precision):
+    """The standalone product at the edges of its tiles: one rounding per product
+    and sum (FP32: of the value and of x), as in the parity tests of larger ones."""
+    rng = np.random.default_rng(5)
+    rows = np.repeat(np.arange(len(lens)), lens)
+    cols = np.concatenate([np.sort(rng.choice(N, k, replace=False)) for k in lens]).astype(int)
+    A = I.CSR.from_scipy(sp.csr_matrix((rng.standard_normal(cols.size), (rows, cols)), shape=(len(lens), N)))
+    Q = I.CSR.from_scipy(sp.identity(N, format="csr"))
+    sol = pdhcg.Solver(I.QP(Q, A, np.ones(len(lens)), np.zeros(N)), pdhcg.Settings(power_iters=1))
+    x = rng.standard_normal(N)
+    got = sol.spmv(1, x, precision=precision).cpu().numpy()
+    ref = O.matvec(A, x)
+    scale = O.matvec(I.CSR(A.nrows, A.ncols, A.rowptr, A.col, np.abs(A.val)), np.abs(x)) + 1e-300
+    assert np.max(np.abs(got - ref) / scale) <= (2 * 2.0 ** -24 * 1.01 if precision else 1e-14)
+    got = sol.spmv(2, np.arange(1.0, len(lens) + 1)).cpu().numpy()
+    ref = O.matvec_t(A, np.arange(1.0, len(lens) + 1))
+    assert np.max(np.abs(got - ref)) <= 1e-12 * max(1.0, np.abs(ref).max())
+    sol.close()
