@@ -2028,12 +2028,16 @@ hipError_t launch_batch(pdhcg_batch* h, bool teams, hipStream_t stream) {
   const int64_t nbars = (int64_t)((teams ? h->nteams : 0) + (shared ? 1 : 0)) * kBarWords;
   hipError_t e = launch_batch_clock(bp.t0, bars, nbars, teams ? h->d_queue : nullptr, (uint32_t)h->nteams,
                                     h->power.out, stream);
-  if (e == hipSuccess && shared) {
-    bp.norm = h->power.out;
-    e = launch_power(kBatchBlock, h->power, h->power_wgs, stream);
-  }
   if (e != hipSuccess) return e;
-  if (teams) return launch_batch_teams(h->any_dense, bp, h->team_grid, stream);
+  if (shared) {  // (a launch that is refused leaves the norm to the members)
+    bp.norm = h->power.out;
+    if (launch_power(kBatchBlock, h->power, h->power_wgs, stream) != hipSuccess) (void)hipGetLastError();
+  }
+  if (teams) {
+    if (launch_batch_teams(h->any_dense, bp, h->team_grid, stream) == hipSuccess) return hipSuccess;
+    (void)hipGetLastError();  // refused (the card cannot hold the grid now): a workgroup per instance
+    bp.order = h->d_order;
+  }
   if (z) return launch_batch_512(bp, h->count, stream);
   return h->any_dense ? launch_batch_256(bp, h->count, stream) : launch_batch_sparse(bp, h->count, stream);
 }
