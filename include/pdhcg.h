@@ -293,8 +293,9 @@ int pdhcg_batch_solve(pdhcg_batch* h, const double* x0, const double* y0, double
                       int32_t vec_on_device, pdhcg_result* rs);
 
 /* Threads per workgroup of the batch's kernel: 256 (the default: two
- * instances per CU, four waves on each) or 512 (one instance per CU, eight
- * waves on it).  A batch made by
+ * instances per CU, three where every Q is sparse, four waves on each, and
+ * several workgroups for an instance that would hold the batch up) or 512 (one
+ * instance per CU, eight waves on it).  A batch made by
  * pdhcg_batch_create holds the row partitions for both; the result of a solve
  * differs between the two only in the rounding of its reductions.
  * INVALID_ARGUMENT for another value. */
