@@ -123,8 +123,9 @@ __device__ __forceinline__ void block_reduce(double* s, double* mx, double* lds)
 // over the workgroup and stored as its partials part[slot(k) * nb + b], sums
 // first.  Only the stored values are needed, so the combination over the waves
 // is done by one lane per value (the waves' results side by side in LDS, read
-// once for all values), not by every thread for every value, and the phase's
-// closing barrier is the one of the grid barrier that follows.  lds holds
+// once for all values), not by every thread for every value.  There is no barrier
+// behind that read: the one of the grid barrier that ends a phase serves, and a
+// phase that uses lds again before it has to synchronise first.  lds holds
 // kWaves * (NS + NM) doubles.
 template <int NS, int NM, typename Slot>
 __device__ __forceinline__ void store_partials(double* s, double* mx, const Slot& slot, double* part, int nb, int b,

@@ -531,6 +531,9 @@ __device__ PDHCG_PHASE void phase_ax(const SolveParams& P, Block B, double* lds)
 template <bool DENSE>
 __device__ PDHCG_PHASE void phase_eval_avg(const SolveParams& P, Block B, double* lds, double* svec) {
   phase_nside<DENSE>(P, P.w_n1, B, P.xa, P.ya, nullptr, nullptr, 1, S_AVG0, lds, svec);
+  // the m-side reduces in the same lds: its first wave must have read the n-side's
+  // values (a wave without m-side rows would overwrite them at once)
+  __syncthreads();
   double s1[1] = {0.0}, mx[2] = {0.0, 0.0};
   const double *const bp = uni(P.b), *const yap = uni(P.ya), *const dm = uni(P.dm);
   double* const axp = uni(P.ax_avg);

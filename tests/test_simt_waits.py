@@ -1,0 +1,103 @@
+"""Waits of the solver's kernels, on the CPU: the library built for the host with a
+lane scheduler (tests/simt), so that a wave or a workgroup that runs ahead of the
+others does so on every run.
+
+What the kernels compute must not depend on that order: each case is solved with
+the waves taken from the first to the last and from the last to the first, the
+workgroups of a grid each running until it has to wait, and gives equal bits both
+times; and in FP64 the oracle's counts and point (sums of at most 1200 terms,
+1200 eps = 3e-13 each, growing by less than 1e2 over the few iterations: 1e-10).
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2405_16160_amd import build, instances as I, pdhcg
+
+from simt_host import build as build_host
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    """the host library behind the Python binding, device tensors on the CPU"""
+    import torch
+    with pytest.MonkeyPatch.context() as mp:
+        cpu = torch.device("cpu")
+        mp.setattr(build, "LIB", build_host(str(tmp_path_factory.mktemp("simt"))))
+        mp.setattr(pdhcg, "_lib", None)
+        mp.setattr(pdhcg, "_stream_ptr", lambda: None)
+        mp.setattr(torch, "device", lambda *a: cpu)
+        mp.setattr(torch.cuda, "current_device", lambda: 0)
+        mp.setattr(torch.cuda, "synchronize", lambda: None)
+        lib = pdhcg.lib()
+        lib.simt_tick(100_000)   # (a wait that never ends: over after 5000 polls)
+        yield lib
+        lib.simt_tick(1)
+
+
+def no_rows(n):
+    return I.CSR(0, n, np.zeros(1, np.int64), np.zeros(0, np.int32), np.zeros(0))
+
+
+def sparse_qp(m, long_row=False):
+    """n = 60 (1200 with a row of A beyond 1024 entries), m rows"""
+    if long_row:
+        q = I.random_qp(n=1200, m=8, r_rows=30, q_density=0.01, a_density=0.01, family=21, instance=0)
+        import scipy.sparse as sp
+        rng = np.random.default_rng(5)
+        M = sp.csr_matrix((q.A.val, q.A.col, q.A.rowptr), shape=(8, 1200)).tolil()
+        M[3] = 0.1 * rng.standard_normal(1200)
+        M = M.tocsr()
+        A = I.CSR(8, 1200, M.indptr.astype(np.int64), M.indices.astype(np.int32), M.data)
+        return I.QP(q.Q, A, q.b, q.c)
+    q = I.random_qp(n=60, m=max(m, 1), r_rows=24, q_density=0.1, a_density=0.1, family=22, instance=m)
+    return q if m else I.QP(q.Q, no_rows(60), np.zeros(0), q.c)
+
+
+def both_orders(host, run):
+    out = []
+    for order in (0, 1):
+        host.simt_wave_order(order)
+        out.append(run())
+    host.simt_wave_order(0)
+    return out
+
+
+def check(qp, settings, runs):
+    """runs: (x, y, result) of each order"""
+    (x, y, r), (x1, y1, r1) = runs
+    drop = ("setup_s", "solve_s", "kernel_s")
+    assert np.array_equal(x, x1) and np.array_equal(y, y1)
+    assert all(r[k] == r1[k] for k in r if k not in drop), (r, r1)
+    o = O.solve(qp, O.Settings(tol=settings.tol_rel_kkt, max_iters=settings.max_iters,
+                               eval_period=settings.eval_period))
+    assert (r["iters"], r["cg_iters_total"], r["restarts"]) == (o.iters, o.cg_steps, o.restarts)
+    assert np.linalg.norm(x - o.x) <= 1e-10 * np.linalg.norm(o.x)
+    assert np.linalg.norm(y - o.y) <= 1e-10 * (1 + np.linalg.norm(o.y))
+    assert r["rel_kkt"] == pytest.approx(O.kkt(qp, x, y)["rel_kkt"], rel=1e-8)
+
+
+CASES = {"m=0": (0, False), "m=1": (1, False), "m=24": (24, False), "long row": (8, True)}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_average_evaluation(host, name):
+    """The restart evaluation reduces the average's n-side and m-side one after the
+    other in the same stretch of LDS: solve kernel, batch kernel, and the batch
+    kernel with a dense Q."""
+    qp = sparse_qp(*CASES[name])
+    s = pdhcg.Settings(tol_rel_kkt=1e-9, max_iters=20, eval_period=4, num_blocks=1)
+
+    def single():
+        h = pdhcg.Solver(qp, s)
+        x, y, r = h.solve()
+        return x.numpy().copy(), y.numpy().copy(), r
+
+    check(qp, s, both_orders(host, single))
+    check(qp, s, both_orders(host, lambda: pdhcg.solve_batch([qp], s)[0]))
+    if qp.n == 60:
+        full = I.portfolio_qp(3, n=60)
+        full = I.QP(full.Q, qp.A, qp.b, qp.c)
+        check(full, s, both_orders(host, lambda: pdhcg.solve_batch([full], s)[0]))
