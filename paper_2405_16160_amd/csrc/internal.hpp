@@ -92,6 +92,11 @@ struct WgPart {
 // Partial-result slots.  Every workgroup writes one value per slot; after a
 // grid barrier every workgroup reduces all of them in the same fixed order,
 // so every workgroup holds bit-identical scalars and takes the same decisions.
+// A slot is written again only after another barrier: until then a workgroup may
+// still be reading it.  The steps of the single-reduction CG, which have one
+// barrier each, take turns with two pairs of slots for that (cg_partials); where
+// other phases would rewrite at once what the last reduction read, a barrier
+// comes between (drive).
 enum Slot {
   // n-side pass at the current point: g = Qx + A'y + c
   S_GG = 0,      // sum g^2                (= rho_0 of CG: r_0 = -g)
@@ -110,6 +115,8 @@ enum Slot {
   // CG and restart
   S_PQ = S_AVG_END,  // sum p.q
   S_RR,          // sum r.r
+  S_PQ_ODD,      // the same for odd steps of the single-reduction CG
+  S_RR_ODD,
   S_DX,          // sum (x_c - x_anchor)^2
   S_DY,          // sum (y_c - y_anchor)^2
   S_FLAG,        // max of a per-workgroup flag (time limit)

@@ -48,6 +48,12 @@ __device__ __forceinline__ int trial_slot(int k) {
   return S_TVIOL + (int)((table >> (4 * k)) & 15);
 }
 
+// where step l of the single-reduction CG has its S_PQ and S_RR
+__device__ __forceinline__ double* cg_partials(double* part, int l, int nb) {
+  static_assert(S_RR == S_PQ + 1 && S_PQ_ODD == S_PQ + 2 && S_RR_ODD == S_RR + 2, "two pairs of slots");
+  return part + (l & 1) * (S_PQ_ODD - S_PQ) * nb;
+}
+
 // ------------------------------------------------------------------ phases
 
 // One workgroup computes out_i = sum_j M[i,j] v_j for a dense symmetric n x n
@@ -814,7 +820,8 @@ __device__ PDHCG_PHASE void phase_cgcg(const SolveParams& P, Block B, const V* q
   else
     run(GatherCG<double>{r_prev, u_prev, s_prev2, alpha, beta, l});
   double dummy[1] = {0.0};
-  store_partials<2, 0>(s, dummy, [](int k) { return k == 0 ? S_RR : S_PQ; }, P.part, B.nb, B.b, lds);
+  store_partials<2, 0>(s, dummy, [](int k) { return k == 0 ? S_RR : S_PQ; }, cg_partials(P.part, l, B.nb), B.nb, B.b,
+                       lds);
 }
 
 // Dual step and averages (Alg. 1): u = A x^{k+1};
@@ -1080,6 +1087,15 @@ enum Op : int32_t {
   OP_COMMIT,       // adaptive step size: the accepted trial becomes the iterate
   OP_RETRY,        // adaptive step size: a rejected trial, back to x^k
 };
+
+// the reduction behind the phase reads the current point's partials; the phase
+// writes some of them
+__device__ __forceinline__ bool reads_point(int op) {
+  return op == OP_NSIDE || op == OP_CERTIFY || op == OP_LIMIT_AX;
+}
+__device__ __forceinline__ bool writes_point(int op) {
+  return op == OP_NSIDE || op == OP_CERTIFY || op == OP_LIMIT_AX || op == OP_DUAL;
+}
 
 struct Ctl {
   SolverState S;
@@ -1539,11 +1555,12 @@ __device__ __forceinline__ ChainEnd cg_chain(const SolveParams& P, Block B, Grid
     };
     if (t.nr > 0) tile_rows_staged<false>(t, G, src, src, put, pre, epi);
     double dummy[1] = {0.0};
-    store_partials<2, 0>(s2, dummy, [](int k) { return k == 0 ? S_RR : S_PQ; }, P.part, B.nb, B.b, lds);
+    double* const part = cg_partials(P.part, l, B.nb);
+    store_partials<2, 0>(s2, dummy, [](int k) { return k == 0 ? S_RR : S_PQ; }, part, B.nb, B.b, lds);
     if (!gs.sync()) return ChainEnd{gs.epoch, 0};
     gather(v_new);  // the next step reads the copy this step wrote
     double gd[2];
-    reduce_sums<S_RR, S_PQ>(P.part, B.nb, gd);
+    reduce_sums<S_RR, S_PQ>(part, B.nb, gd);
     // the control step of a CG phase (control(), OP_CG) while the chain goes on
     const double gl = uniform(gd[0]), dl = uniform(gd[1]);
     const bool stop = l > 0 && ((P.cg_rule == 0 && tau * sqrt(gl) <= eps) || !(gl > 0.0));
@@ -1745,7 +1762,7 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
       case OP_CG:
         if (C.l < P.max_cg) {
           double gd[2];
-          reduce_sums<S_RR, S_PQ>(P.part, B.nb, gd);
+          reduce_sums<S_RR, S_PQ>(cg_partials(P.part, C.l, B.nb), B.nb, gd);
           a = gd[0];
           b = gd[1];
         }
@@ -1772,6 +1789,7 @@ __device__ bool drive(const SolveParams& P, Block B, GridSync& gs, Ctl& C, doubl
       control(P, C, op);
     }
     __syncthreads();
+    if (B.nb > 1 && reads_point(op) && writes_point(C.op) && !(ok = gs.sync())) break;
   }
   return ok;
 }

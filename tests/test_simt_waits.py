@@ -101,3 +101,33 @@ def test_average_evaluation(host, name):
         full = I.portfolio_qp(3, n=60)
         full = I.QP(full.Q, qp.A, qp.b, qp.c)
         check(full, s, both_orders(host, lambda: pdhcg.solve_batch([full], s)[0]))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("form", [1, 2])
+def test_partials_of_the_next_phase(host, form, precision):
+    """A workgroup that is through a barrier and on to its next partial sums while
+    another has yet to read those of before: CG steps with one barrier each (form 1;
+    FP32: the chained steps), and the point's residuals formed anew before a stop
+    (FP32: certified) and at the iteration limit."""
+    qp = sparse_qp(1)
+    for tol, iters in ((1e-9, 12), (1e-1, 100)):
+        s = pdhcg.Settings(tol_rel_kkt=tol, max_iters=iters, eval_period=4, num_blocks=2, cg_form=form,
+                           precision=precision)
+
+        def single():
+            h = pdhcg.Solver(qp, s)
+            x, y, r = h.solve()
+            return x.numpy().copy(), y.numpy().copy(), r
+
+        runs = both_orders(host, single)
+        if precision == 0:
+            check(qp, s, runs)
+        else:   # (the oracle has no FP32 products: one workgroup's result, 2^-24 of each product, as above)
+            s.num_blocks = 1
+            x1, y1, r1 = single()
+            x, y, r = runs[0]
+            assert np.array_equal(x, runs[1][0]) and np.array_equal(y, runs[1][1])
+            assert (r["status"], r["iters"], r["restarts"]) == (r1["status"], r1["iters"], r1["restarts"])
+            assert np.linalg.norm(x - x1) <= 1e-4 * np.linalg.norm(x1)
+            assert r["rel_kkt"] == pytest.approx(O.kkt(qp, x, y)["rel_kkt"], rel=1e-6)
