@@ -588,10 +588,11 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int kReadAhead = 3 * kWave;
+// the row sums read up to prod[kTileNnz + 3 * kWave], that one included (lane_row_sums)
+constexpr int kReadAhead = 3 * kWave + 1;
 struct TileLds {
   double prod[kWaves][kTileNnz];
-  double ahead[kReadAhead];  // what the row sums read, and drop, behind the last wave's stretch
+  double ahead[kReadAhead];  // read, and dropped, behind the last wave's stretch
 };
 
 // the workgroup's staging area

@@ -22,8 +22,8 @@ REPLACE = [
 ]
 
 
-def build(out_dir, defines=(), extra=()):
-    """Build the host library (and `extra` C++ sources into it) in out_dir; returns its path."""
+def build(out_dir):
+    """Build the host library, with the C++ files of tests/simt, in out_dir; returns its path."""
     src = os.path.join(out_dir, "src")
     os.makedirs(src)
     for f in glob.glob(os.path.join(CSRC, "*")):
@@ -34,16 +34,17 @@ def build(out_dir, defines=(), extra=()):
         for pat, sub in REPLACE:
             text = re.sub(pat, sub, text)
         open(os.path.join(src, name), "w").write(text)
-    shutil.copy(os.path.join(SIMT, "simt.cpp"), src)
-    for f in extra:
+    for f in glob.glob(os.path.join(SIMT, "*.cpp")):
         shutil.copy(f, src)
     flags = ["-O1", "-g0", "-std=c++17", "-fPIC", "-fno-strict-aliasing", "-w", "-I", SIMT, "-I", src, "-I",
-             os.path.join(ROCM, "include"), *[f"-D{d}" for d in defines]]
+             os.path.join(ROCM, "include")]
     clang = os.path.join(ROCM, "llvm", "bin", "clang++")
 
     def one(f):
         obj = f + ".o"
-        subprocess.run([clang, *flags, "-x", "c++", "-c", f, "-o", obj], check=True, capture_output=True, text=True)
+        # (reads.cpp: every load as written, also those whose value is dropped)
+        opt = ["-O0"] if f.endswith("reads.cpp") else []
+        subprocess.run([clang, *flags, *opt, "-x", "c++", "-c", f, "-o", obj], check=True, capture_output=True, text=True)
         return obj
 
     files = glob.glob(os.path.join(src, "*.hip")) + glob.glob(os.path.join(src, "*.cpp"))

@@ -8,7 +8,7 @@ workgroups of a grid each running until it has to wait, and gives equal bits bot
 times; and in FP64 the oracle's counts and point (sums of at most 1200 terms,
 1200 eps = 3e-13 each, growing by less than 1e2 over the few iterations: 1e-10).
 """
-import sys
+import ctypes
 
 import numpy as np
 import pytest
@@ -131,3 +131,12 @@ def test_partials_of_the_next_phase(host, form, precision):
             assert (r["status"], r["iters"], r["restarts"]) == (r1["status"], r1["iters"], r1["restarts"])
             assert np.linalg.norm(x - x1) <= 1e-4 * np.linalg.norm(x1)
             assert r["rel_kkt"] == pytest.approx(O.kkt(qp, x, y)["rel_kkt"], rel=1e-6)
+
+
+@pytest.mark.parametrize("n1,n2", [(512, 0), (450, 60), (449, 1), (448, 64), (64, 448), (0, 512), (511, 1)])
+def test_row_sums_stay_in_the_staging_area(host, n1, n2):
+    """A row of [Q | A'] that fills its tile, summed by a wave, in the last stretch of
+    the staging area: the surplus reads of the shorter part end inside it."""
+    out = (ctypes.c_double * 2)()
+    assert host.simt_row_sums(n1, n2, out) == 0
+    assert list(out) == [n1, 1024.0 * n2]
