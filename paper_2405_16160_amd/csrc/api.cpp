@@ -2009,10 +2009,10 @@ int batch_create_impl(pdhcg_batch** out, int32_t count, const pdhcg_csr* Qs_in, 
 
 namespace {
 
-// The batch's start stamp and its one launch at the handle's workgroup size
-// (the parameter blocks of that size's partitions), with the batch's teams if it
-// has any and they are wanted
-hipError_t launch_batch(pdhcg_batch* h, bool teams, hipStream_t stream) {
+// The batch's start stamp (again: the one of the launch before) and its launch at
+// the handle's workgroup size (the parameter blocks of that size's partitions),
+// with the batch's teams if it has any and they are wanted
+hipError_t launch_batch(pdhcg_batch* h, bool teams, bool again, hipStream_t stream) {
   BatchParams bp = h->bp;
   const int z = h->threads == kBatchSizes[1] ? 1 : 0;
   teams = teams && z == 0 && h->nteams > 0;
@@ -2026,7 +2026,7 @@ hipError_t launch_batch(pdhcg_batch* h, bool teams, hipStream_t stream) {
   const bool shared = h->power_wgs > 0;
   uint64_t* const bars = teams ? h->d_bars : h->power.bar;
   const int64_t nbars = (int64_t)((teams ? h->nteams : 0) + (shared ? 1 : 0)) * kBarWords;
-  hipError_t e = launch_batch_clock(bp.t0, bars, nbars, teams ? h->d_queue : nullptr, (uint32_t)h->nteams,
+  hipError_t e = launch_batch_clock(again ? nullptr : bp.t0, bars, nbars, teams ? h->d_queue : nullptr, (uint32_t)h->nteams,
                                     h->power.out, stream);
   if (e != hipSuccess) return e;
   if (shared) {  // (a launch that is refused leaves the norm to the members)
@@ -2073,8 +2073,8 @@ int batch_solve_impl(pdhcg_batch* h, const double* x0, const double* y0, bool in
   const hipMemcpyKind out_kind = out_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   std::vector<SolverState> st(count);
   for (bool teams = true;; teams = false) {
-    if (h->e0) HIPX(hipEventRecord(h->e0, stream));
-    HIPX(launch_batch(h, teams, stream));
+    if (teams && h->e0) HIPX(hipEventRecord(h->e0, stream));
+    HIPX(launch_batch(h, teams, !teams, stream));
     if (h->e1) HIPX(hipEventRecord(h->e1, stream));
     if (h->pre) {  // x = D2 x~, y = D1 y~
       HIPX(launch_diag(h->x, h->d_d2, h->vn_tot, 0, h->xo, stream));
@@ -2085,7 +2085,8 @@ int batch_solve_impl(pdhcg_batch* h, const double* x0, const double* y0, bool in
     if (h->vm_tot) HIPX(hipMemcpyAsync(y_out, yr, sizeof(double) * h->vm_tot, out_kind, stream));
     HIPX(hipStreamSynchronize(stream));
     // a team's barrier timed out (its workgroups were kept from running together
-    // by other work on the card): once more, a workgroup per instance
+    // by other work on the card): once more, a workgroup per instance, within the
+    // same time limit; kernel_s covers both launches
     const bool failed = std::any_of(st.begin(), st.end(), [](const SolverState& S) { return S.done < 0; });
     if (!failed) break;
     if (!teams) return fail(PDHCG_ERR_HIP, "the batched solve kernel failed");
@@ -2208,7 +2209,7 @@ extern "C" int pdhcg_batch_autotune(pdhcg_batch* h, int32_t reps, int32_t* threa
     for (int r = 0; r < reps; ++r) {  // a cold solve of every instance; only the launch is timed
       HIPX(hipMemcpyAsync(h->d_given, cold.data(), cold.size(), hipMemcpyHostToDevice, h->stream));
       HIPX(hipEventRecord(h->e0, h->stream));
-      HIPX(launch_batch(h, true, h->stream));
+      HIPX(launch_batch(h, true, false, h->stream));
       HIPX(hipEventRecord(h->e1, h->stream));
       HIPX(hipStreamSynchronize(h->stream));
       float ms = 0.0f;

@@ -20,7 +20,7 @@ __global__ void __launch_bounds__(kSolveBlock) pdhcg_batch_kernel(BatchParams BP
 __global__ void batch_clock_kernel(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first,
                                    double* norm) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) *t0 = wall_clock64();
+  if (i == 0 && t0) *t0 = wall_clock64();
   if (i == 0 && queue) *queue = first;
   if (i == 0 && norm) *norm = -1.0;
   for (int64_t k = i; k < nbars; k += (int64_t)gridDim.x * blockDim.x) bars[k] = 0;

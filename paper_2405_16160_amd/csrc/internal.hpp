@@ -309,9 +309,9 @@ int solve_batch_in_region(int32_t count, const pdhcg_csr* Qs, const pdhcg_csr* A
 
 // the batched kernel with 256 (batch_kernels.hip; batch_kernels_sparse.hip when
 // every Q is sparse) or 512 threads per workgroup (batch_kernels_512.hip); the
-// clock kernel stamps the batch's start
-// (and clears the barrier words that the launch uses, sets the queue of one with
-// teams and marks the shared norm as not formed)
+// clock kernel stamps the batch's start (t0 null: keeps the stamp), clears the
+// barrier words that the launch uses, sets the queue of one with teams and marks
+// the shared norm as not formed
 hipError_t launch_batch_clock(uint64_t* t0, uint64_t* bars, int64_t nbars, uint32_t* queue, uint32_t first,
                               double* norm, hipStream_t s);
 // the 256-thread kernels with teams (batch_kernels_team.hip): `grid` co-resident workgroups; batch_resident

@@ -7,12 +7,9 @@
 
 #include <sys/mman.h>
 
-#include <chrono>
 #include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
-#include <map>
-#include <memory>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -27,9 +24,9 @@ namespace {
 
 constexpr size_t kStack = 256 << 10;
 int g_descending = 0;              // waves from the last to the first
-int g_refuse = 0;                  // cooperative launches to refuse
+int g_refuse = 0, g_late = 0;      // cooperative launches to refuse; to run with waits that are over at once
 uint64_t g_tick = 1, g_clock = 0;  // ticks per reading of the clock
-int g_coop = 0;                    // cooperative launches that ran
+int g_coop = 0, g_plain = 0;       // launches that ran
 int g_cus = 64, g_per_cu = 2;
 
 __attribute__((naked, noinline)) void switch_to(void**, void*) {
@@ -210,6 +207,11 @@ hipError_t launch_cooperative(dim3 grid, dim3 block, unsigned lds, const std::fu
   }
   if (nb > g_cus * g_per_cu) return hipErrorCooperativeLaunchTooLarge;
   ++g_coop;
+  const uint64_t tick = g_tick;
+  if (g_late > 0) {
+    --g_late;
+    g_tick = 600000000;  // (6 s)
+  }
   Turns turns;
   turns.alive.assign(nb, 1);
   std::vector<char> ok(nb, 0);
@@ -227,6 +229,7 @@ hipError_t launch_cooperative(dim3 grid, dim3 block, unsigned lds, const std::fu
       turns.pass(b, true);
     });
   for (std::thread& t : threads) t.join();
+  g_tick = tick;
   for (char o : ok)
     if (!o) return hipErrorLaunchFailure;
   return hipSuccess;
@@ -251,6 +254,7 @@ char* dynamic_lds() { return (char*)dyn.data(); }
 
 hipError_t launch(dim3 grid, dim3 block, const std::function<void()>& body) {
   bool ok = true;
+  ++g_plain;
   // (on a thread of its own: a workgroup's LDS is thread-local)
   std::thread([&] {
     for (int b = 0; b < (int)(grid.x * grid.y * grid.z) && ok; ++b) {
@@ -282,10 +286,12 @@ extern "C" {
 
 void simt_wave_order(int descending) { simt::g_descending = descending; }
 void simt_refuse(int launches) { simt::g_refuse = launches; }
+void simt_late(int launches) { simt::g_late = launches; }
 void simt_tick(uint64_t ticks) { simt::g_tick = ticks; }
-int simt_cooperative_launches() {
-  const int n = simt::g_coop;
-  simt::g_coop = 0;
+// launches since the last call: cooperative ones * 1000 + the others
+int simt_launches() {
+  const int n = simt::g_coop * 1000 + simt::g_plain;
+  simt::g_coop = simt::g_plain = 0;
   return n;
 }
 
@@ -347,21 +353,21 @@ hipError_t hipGetSymbolAddress(void** p, const void* s) {
   *p = const_cast<void*>(s);
   return hipSuccess;
 }
+// events: readings of the kernels' clock (100 MHz)
 hipError_t hipEventCreate(hipEvent_t* e) {
-  *e = (hipEvent_t) new std::chrono::steady_clock::time_point;
+  *e = (hipEvent_t) new uint64_t;
   return hipSuccess;
 }
 hipError_t hipEventDestroy(hipEvent_t e) {
-  delete (std::chrono::steady_clock::time_point*)e;
+  delete (uint64_t*)e;
   return hipSuccess;
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
-  *(std::chrono::steady_clock::time_point*)e = std::chrono::steady_clock::now();
+  *(uint64_t*)e = simt::g_clock;
   return hipSuccess;
 }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
-  auto t = [](hipEvent_t e) { return *(std::chrono::steady_clock::time_point*)e; };
-  *ms = std::chrono::duration<float, std::milli>(t(b) - t(a)).count();
+  *ms = 1e-5f * (float)(*(uint64_t*)b - *(uint64_t*)a);
   return hipSuccess;
 }
 

@@ -140,3 +140,62 @@ def test_row_sums_stay_in_the_staging_area(host, n1, n2):
     out = (ctypes.c_double * 2)()
     assert host.simt_row_sums(n1, n2, out) == 0
     assert list(out) == [n1, 1024.0 * n2]
+
+
+def team_qps(shared):
+    """two QPs that get teams of workgroups, and one that does not; shared: one Q and A"""
+    if shared:
+        fam = I.mpc_family(T=24, nx=10, nu=4)
+        rng = np.random.default_rng(3)
+        return [I.QP(fam.Q, fam.A, fam.b_for(0.1 * rng.standard_normal(fam.nx)), fam.c) for _ in range(3)]
+    return [I.random_qp(n=n, m=n // 2, r_rows=n // 2, q_density=0.02, a_density=0.02, family=22, instance=i)
+            for i, n in enumerate((700, 40, 300))]
+
+
+def solve_handle(qps, s, threads=256):
+    b = pdhcg.Batch(qps, s)
+    b.set_threads(threads)
+    x, y, rs = b.solve()
+    out = x.numpy().copy(), y.numpy().copy(), rs
+    b.close()
+    return out
+
+
+CAPPED = dict(tol_rel_kkt=1e-12, max_iters=5, eval_period=2, cg_rule=1, max_cg_iters=3, power_iters=20)
+
+
+@pytest.mark.parametrize("fault", ["refuse", "late"])
+@pytest.mark.parametrize("shared", [False, True])
+def test_batch_without_its_teams(host, shared, fault):
+    """The cooperative launches of a batch (the shared norm's, the teams') refused, or
+    their barriers timing out: the batch is solved a workgroup per instance, to the
+    512-thread result."""
+    qps, s = team_qps(shared), pdhcg.Settings(**CAPPED)
+    want = solve_handle(qps, s, threads=512)
+    host.simt_launches()
+    teams = solve_handle(qps, s)
+    assert host.simt_launches() // 1000 == (2 if shared else 1)
+    (host.simt_refuse if fault == "refuse" else host.simt_late)(4)
+    plain = solve_handle(qps, s)
+    host.simt_refuse(0)
+    host.simt_late(0)
+    for x, y, rs in (teams, plain):
+        assert [r["iters"] for r in rs] == [5] * 3
+        for r, w in zip(rs, want[2]):
+            assert r["norm_A"] == pytest.approx(w["norm_A"], rel=1e-12)
+        assert np.linalg.norm(x - want[0]) <= 1e-10 * np.linalg.norm(want[0])
+        assert np.linalg.norm(y - want[1]) <= 1e-10 * np.linalg.norm(want[0])
+
+
+def test_time_limit_covers_the_second_launch(host):
+    """A batch whose first launch ended in a barrier's time-out (5 s) is solved again
+    within the same limit of 5.5 s, and kernel_s covers both launches."""
+    qps, s = team_qps(False), pdhcg.Settings(**{**CAPPED, "time_limit_s": 5.5})
+    host.simt_tick(1)
+    host.simt_launches()
+    host.simt_late(1)
+    x, y, rs = solve_handle(qps, s)
+    host.simt_tick(100_000)
+    assert host.simt_launches() == 1003   # the teams' launch; two that set up a launch and the one without teams
+    assert [r["status_name"] for r in rs] == ["TIME_LIMIT"] * 3
+    assert all(r["iters"] == 0 and r["kernel_s"] > 5.0 for r in rs)
