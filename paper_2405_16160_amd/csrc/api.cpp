@@ -2042,6 +2042,11 @@ hipError_t launch_batch(pdhcg_batch* h, bool teams, bool again, hipStream_t stre
   return h->any_dense ? launch_batch_256(bp, h->count, stream) : launch_batch_sparse(bp, h->count, stream);
 }
 
+// a team's barrier timed out in the launch that left these states
+bool barrier_failed(const std::vector<SolverState>& st) {
+  return std::any_of(st.begin(), st.end(), [](const SolverState& S) { return S.done < 0; });
+}
+
 // Solve every instance of a packed batch.  x0 / y0: packed start points
 // (device pointers when in_dev; may be null) with per-instance flags in
 // `given` (bit 0 x0, bit 1 y0; null: every instance takes the given vectors);
@@ -2084,11 +2089,10 @@ int batch_solve_impl(pdhcg_batch* h, const double* x0, const double* y0, bool in
     HIPX(hipMemcpyAsync(x_out, xr, sizeof(double) * h->vn_tot, out_kind, stream));
     if (h->vm_tot) HIPX(hipMemcpyAsync(y_out, yr, sizeof(double) * h->vm_tot, out_kind, stream));
     HIPX(hipStreamSynchronize(stream));
-    // a team's barrier timed out (its workgroups were kept from running together
-    // by other work on the card): once more, a workgroup per instance, within the
-    // same time limit; kernel_s covers both launches
-    const bool failed = std::any_of(st.begin(), st.end(), [](const SolverState& S) { return S.done < 0; });
-    if (!failed) break;
+    // (a team's workgroups were kept from running together by other work on the
+    // card): once more, a workgroup per instance, within the same time limit;
+    // kernel_s covers both launches
+    if (!barrier_failed(st)) break;
     if (!teams) return fail(PDHCG_ERR_HIP, "the batched solve kernel failed");
   }
   const double t_solve = now_s() - t0;
@@ -2201,6 +2205,7 @@ extern "C" int pdhcg_batch_autotune(pdhcg_batch* h, int32_t reps, int32_t* threa
   if (reps < 1) return fail(PDHCG_ERR_INVALID_ARGUMENT, "reps must be >= 1");
   if (h->nsizes != 2 || !h->e0) return fail(PDHCG_ERR_INVALID_ARGUMENT, "the batch was not made by pdhcg_batch_create");
   const std::vector<uint8_t> cold((size_t)h->count, 0);
+  std::vector<SolverState> st((size_t)h->count);
   double best = INFINITY;
   int32_t pick = h->threads;
   for (int z = 0; z < 2; ++z) {
@@ -2208,10 +2213,15 @@ extern "C" int pdhcg_batch_autotune(pdhcg_batch* h, int32_t reps, int32_t* threa
     double tmin = INFINITY;
     for (int r = 0; r < reps; ++r) {  // a cold solve of every instance; only the launch is timed
       HIPX(hipMemcpyAsync(h->d_given, cold.data(), cold.size(), hipMemcpyHostToDevice, h->stream));
-      HIPX(hipEventRecord(h->e0, h->stream));
-      HIPX(launch_batch(h, true, false, h->stream));
-      HIPX(hipEventRecord(h->e1, h->stream));
-      HIPX(hipStreamSynchronize(h->stream));
+      for (bool teams = true;; teams = false) {  // (without teams if a barrier of theirs timed out)
+        HIPX(hipEventRecord(h->e0, h->stream));
+        HIPX(launch_batch(h, teams, false, h->stream));
+        HIPX(hipEventRecord(h->e1, h->stream));
+        HIPX(hipMemcpyAsync(st.data(), h->d_st, sizeof(SolverState) * h->count, hipMemcpyDeviceToHost, h->stream));
+        HIPX(hipStreamSynchronize(h->stream));
+        if (!barrier_failed(st)) break;
+        if (!teams) return fail(PDHCG_ERR_HIP, "the batched solve kernel failed");
+      }
       float ms = 0.0f;
       HIPX(hipEventElapsedTime(&ms, h->e0, h->e1));
       tmin = std::min(tmin, 1e-3 * (double)ms);

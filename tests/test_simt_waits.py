@@ -199,3 +199,16 @@ def test_time_limit_covers_the_second_launch(host):
     assert host.simt_launches() == 1003   # the teams' launch; two that set up a launch and the one without teams
     assert [r["status_name"] for r in rs] == ["TIME_LIMIT"] * 3
     assert all(r["iters"] == 0 and r["kernel_s"] > 5.0 for r in rs)
+
+
+def test_autotune_repeats_a_launch_that_timed_out(host):
+    """A 256-thread repetition whose teams' barrier timed out is timed again without
+    teams, not taken as it is: one launch with teams, then two pairs of the clock and a
+    batch kernel, at 256 and at 512 threads."""
+    b = pdhcg.Batch(team_qps(False), pdhcg.Settings(**CAPPED))
+    host.simt_launches()
+    host.simt_late(1)
+    t = b.autotune(1)
+    b.close()
+    assert host.simt_launches() == 1005
+    assert t["kernel_s"][256] < 5.0 and t["kernel_s"][512] < 5.0
