@@ -194,7 +194,9 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, double* x_o
  * pdhcg_batch_solve, pdhcg_batch_destroy).  The CSR matrices may be host or
  * device arrays (their on_device flags); bs, cs, x0s, y0s, x_outs, y_outs are
  * host arrays.  Every instance is solved by one workgroup of a persistent
- * kernel and gets its own status in rs[i].  x0s/y0s may be NULL (cold start)
+ * kernel, or by a team of them (see the batches below, which also says when the
+ * last bits of a result depend on that), and gets its own status in rs[i].
+ * x0s/y0s may be NULL (cold start)
  * or hold NULL entries. */
 int pdhcg_solve_batch(int32_t count, const pdhcg_csr* Qs, const pdhcg_csr* As,
                       const double* const* bs, const double* const* cs,
@@ -261,7 +263,18 @@ int pdhcg_solve_multi_rhs(int32_t count, const pdhcg_csr* Q, const pdhcg_csr* A,
 
 /* ----------------------------------------------------------------- batches
  * A batch of independent QPs packed into device memory once and solved any
- * number of times (Alg. 1 on every instance, one workgroup per instance).
+ * number of times (Alg. 1 on every instance).  An instance has one workgroup, or,
+ * in a batch that a few large ones would hold up, a team of up to eight that
+ * run at the same time (pdhcg_batch_teams).  Which instances get a team is
+ * decided from all members, and the sums of one with a team are taken in another
+ * order: the last bits of an instance's result depend on what it is solved with.
+ * They are the same every time as long as the teams get their workgroups at the
+ * same time; a launch that is refused them, or whose workgroups wait 5 s for one
+ * another because other work has the card, is replaced by one without teams,
+ * with the rounding of that.  Batches with teams, and the norm of a matrix A
+ * that all members share, are cooperative launches, which the runtime does not
+ * run side by side on one device: two such batches on two streams solve one
+ * after the other.
  * Vectors of the instances are packed end to end: x of instance i occupies
  * entries n_off[i] .. n_off[i+1]-1 of a packed n-vector, y of instance i
  * entries m_off[i] .. m_off[i+1]-1 of a packed m-vector (pdhcg_batch_layout). */
@@ -287,8 +300,9 @@ int pdhcg_batch_layout(const pdhcg_batch* h, int64_t* n_off, int64_t* m_off);
  * start (0, 0); y0 is projected onto y >= 0) and write the returned points to
  * the packed x_out / y_out.  All four are device pointers when
  * vec_on_device = 1, else host pointers.  rs (count entries, may be NULL)
- * receives each instance's result; kernel_s is the device time of the one
- * batched launch.  Solve outcomes are per instance (rs[i].status). */
+ * receives each instance's result; kernel_s is the device time of the batch's
+ * launches (of both, when one with teams had to be replaced; time_limit_s also
+ * counts from the first).  Solve outcomes are per instance (rs[i].status). */
 int pdhcg_batch_solve(pdhcg_batch* h, const double* x0, const double* y0, double* x_out, double* y_out,
                       int32_t vec_on_device, pdhcg_result* rs);
 
@@ -300,6 +314,11 @@ int pdhcg_batch_solve(pdhcg_batch* h, const double* x0, const double* y0, double
  * differs between the two only in the rounding of its reductions.
  * INVALID_ARGUMENT for another value. */
 int pdhcg_batch_set_threads(pdhcg_batch* h, int32_t threads);
+
+/* How many instances get a team of workgroups when the batch is solved with 256
+ * threads (*planned), and how many had one in the last launch (*used: 0 after a
+ * solve with 512 threads, one whose launch with teams was replaced, or none). */
+int pdhcg_batch_teams(const pdhcg_batch* h, int32_t* planned, int32_t* used);
 
 /* Autotuner of the batched kernel: solve every instance of the batch from a
  * cold start `reps` times with each workgroup size (256 and 512 threads, with

@@ -1385,6 +1385,7 @@ struct pdhcg_batch {
   uint64_t* d_bars = nullptr;
   uint32_t* d_queue = nullptr;
   int32_t team_wgs = 0, nteams = 0, team_grid = 0;  // (no teams: nteams = 0)
+  int32_t teams_used = 0;            // of the last launch
   PowerParams power{};               // ||A|| once for all members, where they share A
   int32_t power_wgs = 0;             // (0: every member forms its own)
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -2017,6 +2018,7 @@ hipError_t launch_batch(pdhcg_batch* h, bool teams, bool again, hipStream_t stre
   const int z = h->threads == kBatchSizes[1] ? 1 : 0;
   teams = teams && z == 0 && h->nteams > 0;
   bp.params = h->d_params + (size_t)z * h->count;
+  h->teams_used = 0;
   if (teams) {
     bp.order = h->d_team_order;
     bp.tasks = h->d_tasks;
@@ -2034,7 +2036,10 @@ hipError_t launch_batch(pdhcg_batch* h, bool teams, bool again, hipStream_t stre
     if (launch_power(kBatchBlock, h->power, h->power_wgs, stream) != hipSuccess) (void)hipGetLastError();
   }
   if (teams) {
-    if (launch_batch_teams(h->any_dense, bp, h->team_grid, stream) == hipSuccess) return hipSuccess;
+    if (launch_batch_teams(h->any_dense, bp, h->team_grid, stream) == hipSuccess) {
+      h->teams_used = h->nteams;
+      return hipSuccess;
+    }
     (void)hipGetLastError();  // refused (the card cannot hold the grid now): a workgroup per instance
     bp.order = h->d_order;
   }
@@ -2197,6 +2202,13 @@ extern "C" int pdhcg_batch_set_threads(pdhcg_batch* h, int32_t threads) {
     return fail(PDHCG_ERR_INVALID_ARGUMENT,
                 "threads per workgroup must be 256, or 512 for a batch made by pdhcg_batch_create");
   h->threads = threads;
+  return 0;
+}
+
+extern "C" int pdhcg_batch_teams(const pdhcg_batch* h, int32_t* planned, int32_t* used) {
+  if (!h || !planned || !used) return fail(PDHCG_ERR_INVALID_ARGUMENT, "null handle or output");
+  *planned = h->nteams;
+  *used = h->teams_used;
   return 0;
 }
 

@@ -79,7 +79,7 @@ EXPORTS = ["pdhcg_default_settings", "pdhcg_create", "pdhcg_create_lowrank", "pd
            "pdhcg_solve_multi_rhs", "pdhcg_spmv", "pdhcg_get_scaling",
            "pdhcg_autotune", "pdhcg_plan_info", "pdhcg_destroy", "pdhcg_error_string", "pdhcg_last_error",
            "pdhcg_batch_create", "pdhcg_batch_layout", "pdhcg_batch_solve", "pdhcg_batch_get_scaling",
-           "pdhcg_batch_set_threads", "pdhcg_batch_autotune", "pdhcg_batch_destroy"]
+           "pdhcg_batch_set_threads", "pdhcg_batch_teams", "pdhcg_batch_autotune", "pdhcg_batch_destroy"]
 
 
 class PdhcgError(RuntimeError):
@@ -134,6 +134,7 @@ def lib():
         L.pdhcg_batch_solve.argtypes = [P, P, P, P, P, C.c_int32, P]
         L.pdhcg_batch_get_scaling.argtypes = [P, P, P, C.c_int32]
         L.pdhcg_batch_set_threads.argtypes = [P, C.c_int32]
+        L.pdhcg_batch_teams.argtypes = [P, P, P]
         L.pdhcg_batch_autotune.argtypes = [P, C.c_int32, P, P]
         L.pdhcg_batch_destroy.argtypes = [P]
         L.pdhcg_batch_destroy.restype = None
@@ -474,6 +475,12 @@ class Batch:
         """Threads per workgroup of the batched kernel: 256 (default) or 512."""
         _check(lib().pdhcg_batch_set_threads(self.h, threads))
         self.threads = threads
+
+    def teams(self) -> tuple:
+        """(instances that get a team of workgroups, those that had one in the last launch)"""
+        planned, used = C.c_int32(), C.c_int32()
+        _check(lib().pdhcg_batch_teams(self.h, C.byref(planned), C.byref(used)))
+        return planned.value, used.value
 
     def autotune(self, reps: int = 1) -> dict:
         """Time cold solves of the whole batch at 256 and 512 threads per

@@ -143,7 +143,7 @@ def test_row_sums_stay_in_the_staging_area(host, n1, n2):
 
 
 def team_qps(shared):
-    """two QPs that get teams of workgroups, and one that does not; shared: one Q and A"""
+    """a QP that gets a team of workgroups among others; shared: three with one Q and A"""
     if shared:
         fam = I.mpc_family(T=24, nx=10, nu=4)
         rng = np.random.default_rng(3)
@@ -156,7 +156,7 @@ def solve_handle(qps, s, threads=256):
     b = pdhcg.Batch(qps, s)
     b.set_threads(threads)
     x, y, rs = b.solve()
-    out = x.numpy().copy(), y.numpy().copy(), rs
+    out = x.numpy().copy(), y.numpy().copy(), rs, b.teams()
     b.close()
     return out
 
@@ -179,7 +179,10 @@ def test_batch_without_its_teams(host, shared, fault):
     plain = solve_handle(qps, s)
     host.simt_refuse(0)
     host.simt_late(0)
-    for x, y, rs in (teams, plain):
+    # (the large QP or all three of the family; none with 512 threads or after the fault)
+    n = 3 if shared else 1
+    assert (want[3], teams[3], plain[3]) == ((n, 0), (n, n), (n, 0))
+    for x, y, rs, _ in (teams, plain):
         assert [r["iters"] for r in rs] == [5] * 3
         for r, w in zip(rs, want[2]):
             assert r["norm_A"] == pytest.approx(w["norm_A"], rel=1e-12)
@@ -194,7 +197,7 @@ def test_time_limit_covers_the_second_launch(host):
     host.simt_tick(1)
     host.simt_launches()
     host.simt_late(1)
-    x, y, rs = solve_handle(qps, s)
+    rs = solve_handle(qps, s)[2]
     host.simt_tick(100_000)
     assert host.simt_launches() == 1003   # the teams' launch; two that set up a launch and the one without teams
     assert [r["status_name"] for r in rs] == ["TIME_LIMIT"] * 3
