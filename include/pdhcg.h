@@ -271,10 +271,11 @@ int pdhcg_solve_multi_rhs(int32_t count, const pdhcg_csr* Q, const pdhcg_csr* A,
  * They are the same every time as long as the teams get their workgroups at the
  * same time; a launch that is refused them, or whose workgroups wait 5 s for one
  * another because other work has the card, is replaced by one without teams,
- * with the rounding of that.  Batches with teams, and the norm of a matrix A
- * that all members share, are cooperative launches, which the runtime does not
- * run side by side on one device: two such batches on two streams solve one
- * after the other.
+ * with the rounding of that.  A launch with teams is a cooperative one, as that
+ * of a single QP; the runtime does not run two of those side by side on one
+ * device, so two such batches on two streams solve one after the other (two of
+ * 150 MPC QPs: 42 ms, as long as one after the other alone).  So does the short
+ * launch (about 1 ms) that forms the norm of a matrix A that all members share.
  * Vectors of the instances are packed end to end: x of instance i occupies
  * entries n_off[i] .. n_off[i+1]-1 of a packed n-vector, y of instance i
  * entries m_off[i] .. m_off[i+1]-1 of a packed m-vector (pdhcg_batch_layout). */

@@ -1099,7 +1099,7 @@ int pdhcg_autotune(pdhcg_handle* h, int32_t iters, int32_t* num_blocks, int32_t*
     h->threads = t;
     if ((rc = set_max_nb(h))) break;
     for (int nb : {64, 128, 256, 512}) {
-      if (nb > h->max_nb || nb > 256 * (kSolveBlock / t)) continue;
+      if (nb > h->max_nb) continue;
       for (int g : {-1, 0, 1}) {
         if ((rc = plan_grid(h, nb, g))) break;
         pdhcg_result r;

@@ -394,10 +394,8 @@ struct GridSync {
 
 // ------------------------------------------------------- row-split products
 
-// Value loaders: FP64 or FP32 matrix values, FP64 or FP32 gathered vectors;
-// products are accumulated in FP64.
-template <typename V>
-__device__ __forceinline__ double ldv(const V* p, int k) { return (double)p[k]; }
+// FP64 or FP32 matrix values, FP64 or FP32 gathered vectors; products are
+// accumulated in FP64.
 
 // Load through a global-address-space pointer (the solver's arrays all live
 // in device memory; a generic pointer would make the compiler emit flat loads,
@@ -527,7 +525,7 @@ struct GatherDir2 {
 // ------------------------------------------------------------- wave tiles
 //
 // A sparse product is cut on the host into tiles of whole rows that one wave
-// processes alone: at most kTileNnz entries (8 per lane) and kTileRows rows (2
+// processes alone: at most kTileNnz entries (8 per lane) and kTileRows rows (one
 // per lane), sized so that the waves of a workgroup get equal shares.  The wave
 // loads the tile's row offsets, the rows' own inputs and its entries in one
 // burst, gathers, parks the products in its own stretch of LDS and sums the

@@ -6,7 +6,7 @@
 namespace pdhcg {
 
 // Threads per workgroup.  The cooperative single-QP kernels run 512 (one
-// workgroup per CU); the batched kernel, one workgroup per QP, runs 256 by
+// workgroup per CU); the batched kernel, a workgroup or a team per QP, runs 256 by
 // default so that two instances share a CU at the same register budget (two
 // waves per SIMD), or 512 (one instance per CU) when its autotuner finds that
 // faster.  The solver's device code is compiled once per size: a translation
@@ -26,7 +26,7 @@ constexpr int kLongRow = 1024;    // rows longer than this are reduced by the wh
 
 // Device CSR with 32-bit indices; val32 is an FP32 copy of val (or null).
 // dense = 1 marks a square matrix stored as nrows*ncols row-major values
-// (rowptr and col unused); only the one-workgroup-per-QP kernel takes it.
+// (rowptr and col unused); only the batched kernels take it.
 struct DevMat {
   int32_t nrows, ncols;
   const int32_t* rowptr;

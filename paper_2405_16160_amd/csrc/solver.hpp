@@ -8,9 +8,9 @@
 #include <math.h>
 
 #include "device.hpp"
-#ifndef PDHCG_PHASE
+// a phase is a function of its own: inlined into the driver, the phases together
+// would spill
 #define PDHCG_PHASE __attribute__((noinline))
-#endif
 
 namespace pdhcg {
 
@@ -400,7 +400,7 @@ template <bool DENSE>
 __device__ PDHCG_PHASE void phase_nside(const SolveParams& P, const WgPart& pt, Block B, const double* xv,
                             const double* yv, double* r, float* r32, int r32_stride, int slot0, double* lds,
                             double* svec, int qmode = QX_INTO_Q) {
-  // dense Q (one workgroup per QP): Q xv first, into q or qx, unless qx is kept
+  // dense Q: the own rows of Q xv first, into q or qx, unless qx is kept
   constexpr bool dense = DENSE;
   double* const qsrc = qmode == QX_INTO_Q ? P.q : P.qx;
   if (dense && qmode != QX_KEPT) dense_qx(P, pt, B, xv, svec, qsrc);
@@ -1054,8 +1054,8 @@ __device__ PDHCG_PHASE void reduce_kkt(const SolveParams& P, Block B, int slot0,
 
 // The restarted PDHCG loop (Alg. 1 with the practical rules of Sec. 4),
 // shared by the cooperative single-QP kernel (many workgroups, grid
-// barriers) and the batched kernel (one workgroup per QP, nb = 1, where a
-// barrier is a workgroup barrier).
+// barriers) and the batched kernels (one workgroup per QP, nb = 1, where a
+// barrier is a workgroup barrier, or a team of them).
 //
 // Every thread of the workgroup runs the data-parallel phases and the
 // reductions of their partials; the scalar logic (relKKT tests, restart
