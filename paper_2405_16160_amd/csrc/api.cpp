@@ -1075,7 +1075,7 @@ int pdhcg_spmv(pdhcg_handle* h, int32_t which, int32_t precision, const double* 
   }
   for (int r = 0; r < std::max(repeats, 1); ++r)
     HIPX(launch_spmv_stream(M.rowptr, M.col, M.val, M.val32, precision, x, x32, y, h->stiles[which],
-                            h->nstiles[which], h->stream));
+                            h->nstiles[which], M.ncols, h->l2_bytes, h->stream));
   HIPX(hipStreamSynchronize(h->stream));
   return 0;
 }

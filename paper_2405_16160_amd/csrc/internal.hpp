@@ -333,10 +333,11 @@ hipError_t solve_kernel_lds(int threads, int* static_bytes);
 hipError_t solve_occupancy_dyn(int threads, int dyn_lds, int* per_cu);
 hipError_t launch_power(int threads, const PowerParams& p, int nb, hipStream_t s);
 hipError_t launch_init_point(const SolveParams* p_dev, int64_t n, int64_t m, hipStream_t s);
-// standalone product y = M x over host-cut tiles (spmv_kernels.hip)
+// standalone product y = M x over host-cut tiles (spmv_kernels.hip); ncols is the
+// length of x, l2_bytes one XCD's L2
 hipError_t launch_spmv_stream(const int32_t* rowptr, const int32_t* col, const double* val, const float* val32,
                               int precision, const double* x, const float* x32, double* y, const int32_t* tiles,
-                              int ntiles, hipStream_t s);
+                              int ntiles, int64_t ncols, int64_t l2_bytes, hipStream_t s);
 int spmv_stream_tile_nnz();
 int spmv_stream_tile_rows();
 hipError_t launch_to_f32(const double* in, float* out, int64_t n, hipStream_t s);

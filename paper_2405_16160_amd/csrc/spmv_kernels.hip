@@ -12,10 +12,12 @@
 // (data-parallel-primitive lane moves, no LDS shuffles; a row far longer
 // than its group is summed by a whole wave instead).  A long tile is
 // summed by the whole workgroup in chunks.  Every row's sum is formed in a
-// fixed order, so results are bit-reproducible.  A tile's entries are read once
-// and carry the non-temporal hint, which leaves the L2 to x: power-law A, n = 2e6,
-// FP32, 110.7 -> 106.9 us, bound by the L2 misses of the gathers; a matrix that
-// stays cached loses nothing (n = 1000: 17.6 us both).
+// fixed order, so results are bit-reproducible.  Where x outgrows an XCD's L2
+// (by a quarter, 5 MB), a tile's entries carry the non-temporal hint, which leaves
+// the L2 to x: power-law A, n = 2e6, FP32 (x of 8 MB), 87.8 -> 85.1 us a product, Q
+// 92.9 -> 88.5; random n = 9e5, A, FP64 (7.2 MB) 93.7 -> 88.0.  Where x fits, the
+// hint costs the last-level cache's lines of the matrix: the same A', FP32 (x of 1.8
+// MB), 45.5 us without and 55.3 with it; at 4.8 MB the two are within 1 %.
 #include "device.hpp"
 
 namespace pdhcg {
@@ -51,7 +53,8 @@ __device__ __forceinline__ int stream_group(int mean_len, int nr) {
   return f < g ? f : g;
 }
 
-template <typename V, typename T>
+// NT: the entries are loaded with the non-temporal hint
+template <typename V, typename T, bool NT>
 __global__ void __launch_bounds__(kStreamBlock) spmv_stream_kernel(const int32_t* __restrict__ rowptr,
                                                                    const int32_t* __restrict__ col,
                                                                    const V* __restrict__ val,
@@ -104,8 +107,8 @@ __global__ void __launch_bounds__(kStreamBlock) spmv_stream_kernel(const int32_t
     for (int u = 0; u < kStreamUnroll; ++u) {
       if (u * kStreamBlock >= ne) break;
       const int k = min(u * kStreamBlock + tid, ne - 1);
-      c[u] = gld_nt(col + e0 + k);
-      v[u] = gld_nt(val + e0 + k);
+      c[u] = NT ? gld_nt(col + e0 + k) : gld(col + e0 + k);
+      v[u] = NT ? gld_nt(val + e0 + k) : gld(val + e0 + k);
     }
     double g[kStreamUnroll];
 #pragma unroll
@@ -154,14 +157,14 @@ __global__ void __launch_bounds__(kStreamBlock) spmv_stream_kernel(const int32_t
 
 hipError_t launch_spmv_stream(const int32_t* rowptr, const int32_t* col, const double* val, const float* val32,
                               int precision, const double* x, const float* x32, double* y, const int32_t* tiles,
-                              int ntiles, hipStream_t s) {
+                              int ntiles, int64_t ncols, int64_t l2_bytes, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (precision == 1)
-    hipLaunchKernelGGL((spmv_stream_kernel<float, float>), dim3(ntiles), dim3(kStreamBlock), 0, s, rowptr, col,
-                       val32, x32, y, tiles);
-  else
-    hipLaunchKernelGGL((spmv_stream_kernel<double, double>), dim3(ntiles), dim3(kStreamBlock), 0, s, rowptr, col,
-                       val, x, y, tiles);
+  const bool nt = 4 * ncols * (precision == 1 ? 4 : 8) > 5 * l2_bytes;
+  auto run = [&](auto kernel, const auto* v, const auto* xv) {
+    hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(kStreamBlock), 0, s, rowptr, col, v, xv, y, tiles);
+  };
+  if (precision == 1) run(nt ? spmv_stream_kernel<float, float, true> : spmv_stream_kernel<float, float, false>, val32, x32);
+  else run(nt ? spmv_stream_kernel<double, double, true> : spmv_stream_kernel<double, double, false>, val, x);
   return hipGetLastError();
 }
 
