@@ -45,6 +45,7 @@ SOLVER_SOURCES = ["paper_2405_16160_amd/csrc/solve_kernels.hip", "paper_2405_161
                   "paper_2405_16160_amd/csrc/batch_kernels_team.hip",
                   "paper_2405_16160_amd/csrc/batch_kernels_sparse_team.hip",
                   "paper_2405_16160_amd/csrc/batch_kernels_512.hip", "paper_2405_16160_amd/csrc/solve_kernels_256.hip",
+                  "paper_2405_16160_amd/csrc/solve_kernels_256_streamed.hip",
                   "paper_2405_16160_amd/csrc/solver.hpp", "paper_2405_16160_amd/csrc/device.hpp",
                   "paper_2405_16160_amd/csrc/internal.hpp", "paper_2405_16160_amd/csrc/api.cpp",
                   "include/pdhcg.h"]

@@ -532,12 +532,24 @@ int solve_threads(const pdhcg_handle* h, const pdhcg_settings& s) {
   return (!h->lowrank && 12 * h->n > h->l2_bytes) ? 256 : kSolveBlock;
 }
 
+// Whether the 256-thread kernels stream their matrices past the caches: once the
+// vectors they gather (8 n bytes: x in FP64, or the FP32 (r, p) records of the
+// textbook CG) exceed an XCD's L2 by half.  With the hint against without, random
+// QPs, FP64 / FP32 products, capped at 40 iterations (30 from 7e5 on): n = 2e5 5.78
+// and 5.61 ms / 5.15 and 4.94, 4e5 9.86 and 9.35 / 8.92 and 8.27, 6e5 13.7 and 13.4 /
+// 11.4 and 10.5, 7e5 12.0 both / 9.70 and 9.43, 8e5 13.9 and 14.1 / 10.9 both, 9e5
+// 15.7 and 16.1 / 12.2 and 12.4, 1e6 23.6 and 24.4 / 17.9 and 18.4; power-law n = 2e6
+// 64.6 and 65.4 / 41.9 and 42.6.
+bool streamed_matrices(const pdhcg_handle* h) { return 2 * 8 * h->n > 3 * h->l2_bytes; }
+
+SolveKernel kernel_of(const pdhcg_handle* h) { return SolveKernel{h->threads, streamed_matrices(h)}; }
+
 // the co-resident workgroups of the cooperative kernels at h->threads
 int set_max_nb(pdhcg_handle* h) {
   int dev = 0, cus = 0, per_cu = 0;
   HIPX(hipGetDevice(&dev));
   HIPX(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  HIPX(solve_occupancy(h->threads, &per_cu));
+  HIPX(solve_occupancy(kernel_of(h), &per_cu));
   h->max_nb = std::max(1, std::min(cus * std::max(per_cu, 1), 1024));
   return 0;
 }
@@ -602,7 +614,7 @@ int plan_residency(pdhcg_handle* h, SolveParams& p) {
   HIPX(hipGetDevice(&dev));
   HIPX(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   HIPX(hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev));
-  HIPX(solve_kernel_lds(h->threads, &stat));
+  HIPX(solve_kernel_lds(kernel_of(h), &stat));
   const int per_cu = (h->nb + cus - 1) / std::max(cus, 1);
   const int64_t budget = (int64_t)lds_cu / std::max(per_cu, 1) - stat - 256;
   auto block = [&](const std::vector<int32_t>& bnd, const std::vector<int64_t>& rp) {
@@ -637,7 +649,7 @@ int plan_residency(pdhcg_handle* h, SolveParams& p) {
   p.own_off = (int32_t)(q_end + (p.res_m ? ba : 0));
   if (total > 0) {
     int occ = 0;
-    HIPX(solve_occupancy_dyn(h->threads, (int)total, &occ));
+    HIPX(solve_occupancy_dyn(kernel_of(h), (int)total, &occ));
     if (occ * cus < h->nb) {  // would break co-residency: keep everything in device memory
       p.res_cg = p.res_m = p.own_cg = 0;
       total = 0;
@@ -733,7 +745,7 @@ int estimate_norm(pdhcg_handle* h) {
   pp.pm = h->pm.view();
   pp.iters = h->s.power_iters;
   HIPX(hipMemsetAsync(h->bar, 0, sizeof(uint64_t) * kBarWords, h->stream));
-  HIPX(launch_power(h->threads, pp, h->nb, h->stream));
+  HIPX(launch_power(kernel_of(h), pp, h->nb, h->stream));
   double v = 0.0;
   uint64_t abort_word = 0;
   HIPX(hipMemcpyAsync(&v, h->scratch, sizeof(double), hipMemcpyDeviceToHost, h->stream));
@@ -999,7 +1011,7 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, double* x_o
   for (;;) {
     HIPX(hipMemsetAsync(h->bar, 0, sizeof(uint64_t) * kBarWords, h->stream));
     HIPX(hipEventRecord(h->ev0, h->stream));
-    HIPX(launch_solve(h->threads, h->d_params, h->nb, h->res_bytes, h->stream));
+    HIPX(launch_solve(kernel_of(h), h->d_params, h->nb, h->res_bytes, h->stream));
     HIPX(hipEventRecord(h->ev1, h->stream));
     HIPX(hipMemcpyAsync(&st, h->st, sizeof(st), hipMemcpyDeviceToHost, h->stream));
     HIPX(hipStreamSynchronize(h->stream));
@@ -2058,7 +2070,7 @@ hipError_t launch_batch(pdhcg_batch* h, bool teams, bool again, hipStream_t stre
   if (e != hipSuccess) return e;
   if (shared) {  // (a launch that is refused leaves the norm to the members)
     bp.norm = h->power.out;
-    if (launch_power(kBatchBlock, h->power, h->power_wgs, stream) != hipSuccess) (void)hipGetLastError();
+    if (launch_power(SolveKernel{kBatchBlock, false}, h->power, h->power_wgs, stream) != hipSuccess) (void)hipGetLastError();
   }
   if (teams) {
     if (launch_batch_teams(h->any_dense, bp, h->team_grid, stream) == hipSuccess) {

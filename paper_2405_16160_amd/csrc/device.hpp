@@ -550,10 +550,10 @@ __device__ __forceinline__ T gld_at(const T* base, int k) {
                                                        (uint32_t)k * (uint32_t)sizeof(T));
 }
 
-// An entry of a matrix.  Where the matrix does not fit the caches anyway (the
-// 256-thread cooperative kernels), the load carries the non-temporal hint, which
-// leaves the L2 to the gathered vectors: power-law QP n = 2e6, 7 TB/s of L2 misses,
-// 32.0 -> 31.4 ms for 40 iterations.
+// An entry of a matrix.  Where the gathered vectors outgrow the L2 well
+// (solve_kernels_256_streamed.hip), the load carries the non-temporal hint, which
+// leaves the L2 to them: power-law QP n = 2e6, 7 TB/s of L2 misses, 32.0 -> 31.4 ms
+// for 40 iterations.
 #ifndef PDHCG_STREAMED
 #define PDHCG_STREAMED 0
 #endif

@@ -45,50 +45,52 @@ __global__ void to_f32_kernel(const double* in, float* out, int64_t n) {
 
 // ---------------------------------------------------------------- launchers
 
-// the solve kernel for `threads` per workgroup: this unit's (512 threads), or
-// the 256-thread copy of solve_kernels_256.hip
-static const void* solve_kernel_for(int threads) {
-  return threads == kBlock ? (const void*)pdhcg_solve_kernel : solve_kernel_256();
+// the solve kernel of a handle: this unit's (512 threads), or a 256-thread copy of
+// solve_kernels_256.hip or solve_kernels_256_streamed.hip
+static const void* solve_kernel_for(SolveKernel k) {
+  if (k.threads == kBlock) return (const void*)pdhcg_solve_kernel;
+  return k.streamed ? solve_kernel_256_streamed() : solve_kernel_256();
 }
 
 // the power iteration at the same workgroup size (it walks the same row
 // partitions, whose tiles are sized for it)
-static const void* power_kernel_for(int threads) {
-  return threads == kBlock ? (const void*)pdhcg_power_kernel : power_kernel_256();
+static const void* power_kernel_for(SolveKernel k) {
+  if (k.threads == kBlock) return (const void*)pdhcg_power_kernel;
+  return k.streamed ? power_kernel_256_streamed() : power_kernel_256();
 }
 
-hipError_t launch_solve(int threads, const SolveParams* p_dev, int nb, int dyn_lds, hipStream_t s) {
+hipError_t launch_solve(SolveKernel kernel, const SolveParams* p_dev, int nb, int dyn_lds, hipStream_t s) {
   const SolveParams* pc = p_dev;
   void* args[] = {&pc};
-  const void* k = solve_kernel_for(threads);
+  const void* k = solve_kernel_for(kernel);
   if (dyn_lds > 0) {
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_lds);
     if (e != hipSuccess) return e;
   }
-  return hipLaunchCooperativeKernel(k, dim3(nb), dim3(threads), args, (unsigned)dyn_lds, s);
+  return hipLaunchCooperativeKernel(k, dim3(nb), dim3(kernel.threads), args, (unsigned)dyn_lds, s);
 }
 
-hipError_t solve_kernel_lds(int threads, int* static_bytes) {
+hipError_t solve_kernel_lds(SolveKernel kernel, int* static_bytes) {
   hipFuncAttributes a;
-  hipError_t e = hipFuncGetAttributes(&a, solve_kernel_for(threads));
+  hipError_t e = hipFuncGetAttributes(&a, solve_kernel_for(kernel));
   if (e != hipSuccess) return e;
   *static_bytes = (int)a.sharedSizeBytes;
   return hipSuccess;
 }
 
-hipError_t solve_occupancy_dyn(int threads, int dyn_lds, int* per_cu) {
-  const void* k = solve_kernel_for(threads);
+hipError_t solve_occupancy_dyn(SolveKernel kernel, int dyn_lds, int* per_cu) {
+  const void* k = solve_kernel_for(kernel);
   if (dyn_lds > 0) {
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_lds);
     if (e != hipSuccess) return e;
   }
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k, threads, dyn_lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k, kernel.threads, dyn_lds);
 }
 
-hipError_t launch_power(int threads, const PowerParams& p, int nb, hipStream_t s) {
+hipError_t launch_power(SolveKernel kernel, const PowerParams& p, int nb, hipStream_t s) {
   PowerParams pc = p;
   void* args[] = {&pc};
-  return hipLaunchCooperativeKernel(power_kernel_for(threads), dim3(nb), dim3(threads), args, 0, s);
+  return hipLaunchCooperativeKernel(power_kernel_for(kernel), dim3(nb), dim3(kernel.threads), args, 0, s);
 }
 
 hipError_t launch_init_point(const SolveParams* p_dev, int64_t n, int64_t m, hipStream_t s) {
@@ -100,11 +102,11 @@ hipError_t launch_init_point(const SolveParams* p_dev, int64_t n, int64_t m, hip
   return hipGetLastError();
 }
 
-hipError_t solve_occupancy(int threads, int* per_cu) {
+hipError_t solve_occupancy(SolveKernel kernel, int* per_cu) {
   int a = 0, b = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, solve_kernel_for(threads), threads, 0);
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, solve_kernel_for(kernel), kernel.threads, 0);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, power_kernel_for(threads), threads, 0);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, power_kernel_for(kernel), kernel.threads, 0);
   if (e != hipSuccess) return e;
   *per_cu = a < b ? a : b;
   return hipSuccess;

@@ -5,9 +5,7 @@
 // either way, but two workgroups wait apart, so one's gathers stay in flight
 // while the other sums a tile or waits at a workgroup barrier, at the cost of
 // twice the arrivals at every grid barrier.
-// Its matrices stream past the caches too (non-temporal loads of their entries).
 #define PDHCG_BLOCK_SIZE 256
-#define PDHCG_STREAMED 1
 #include "solver.hpp"
 
 namespace pdhcg {

@@ -27,7 +27,7 @@ int g_descending = 0;              // waves from the last to the first
 int g_refuse = 0, g_late = 0;      // cooperative launches to refuse; to run with waits that are over at once
 uint64_t g_tick = 1, g_clock = 0;  // ticks per reading of the clock
 int g_coop = 0, g_plain = 0;       // launches that ran
-int g_cus = 64, g_per_cu = 2;
+int g_cus = 64, g_per_cu = 2, g_l2 = 4 << 20;
 
 __attribute__((naked, noinline)) void switch_to(void**, void*) {
   asm("pushq %rbp; pushq %rbx; pushq %r12; pushq %r13; pushq %r14; pushq %r15\n"
@@ -274,6 +274,8 @@ hipError_t launch(dim3 grid, dim3 block, const std::function<void()>& body) {
 namespace pdhcg {
 void pdhcg_solve_kernel(const SolveParams*);
 void pdhcg_solve_kernel_wg256(const SolveParams*);
+void pdhcg_solve_kernel_wg256_streamed(const SolveParams*);
+void pdhcg_power_kernel_wg256_streamed(PowerParams);
 void pdhcg_power_kernel(PowerParams);
 void pdhcg_power_kernel_wg256(PowerParams);
 void pdhcg_batch_kernel_team(BatchParams);
@@ -288,6 +290,7 @@ void simt_wave_order(int descending) { simt::g_descending = descending; }
 void simt_refuse(int launches) { simt::g_refuse = launches; }
 void simt_late(int launches) { simt::g_late = launches; }
 void simt_tick(uint64_t ticks) { simt::g_tick = ticks; }
+void simt_l2(int bytes) { simt::g_l2 = bytes; }
 // launches since the last call: cooperative ones * 1000 + the others
 int simt_launches() {
   const int n = simt::g_coop * 1000 + simt::g_plain;
@@ -302,6 +305,8 @@ hipError_t hipLaunchCooperativeKernel(const void* f, dim3 grid, dim3 block, void
   };
   bind(pdhcg_solve_kernel, (const SolveParams**)args[0]);
   bind(pdhcg_solve_kernel_wg256, (const SolveParams**)args[0]);
+  bind(pdhcg_solve_kernel_wg256_streamed, (const SolveParams**)args[0]);
+  bind(pdhcg_power_kernel_wg256_streamed, (PowerParams*)args[0]);
   bind(pdhcg_power_kernel, (PowerParams*)args[0]);
   bind(pdhcg_power_kernel_wg256, (PowerParams*)args[0]);
   bind(pdhcg_batch_kernel_team, (BatchParams*)args[0]);
@@ -336,7 +341,7 @@ hipError_t hipGetDevice(int* d) {
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
-  *v = a == hipDeviceAttributeL2CacheSize ? 4 << 20 : a == hipDeviceAttributeMultiprocessorCount ? simt::g_cus : 160 << 10;
+  *v = a == hipDeviceAttributeL2CacheSize ? simt::g_l2 : a == hipDeviceAttributeMultiprocessorCount ? simt::g_cus : 160 << 10;
   return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }

@@ -215,3 +215,20 @@ def test_autotune_repeats_a_launch_that_timed_out(host):
     b.close()
     assert host.simt_launches() == 1005
     assert t["kernel_s"][256] < 5.0 and t["kernel_s"][512] < 5.0
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_streamed_kernels_equal_the_others(host, precision):
+    """The 256-thread kernels with and without streamed matrices: equal bits.  (n = 60:
+    streamed past an L2 of 320 bytes.)"""
+    qp = sparse_qp(24)
+    out = []
+    for l2 in (320, 319):
+        host.simt_l2(l2)
+        h = pdhcg.Solver(qp, pdhcg.Settings(tol_rel_kkt=1e-9, max_iters=9, eval_period=4, num_blocks=2, threads=256,
+                                            cg_form=2, precision=precision))
+        x, y, r = h.solve()
+        out.append((x.numpy().copy(), y.numpy().copy(), r["rel_kkt"], r["norm_A"]))
+    host.simt_l2(4 << 20)
+    (x, y, k, a), (x1, y1, k1, a1) = out
+    assert np.array_equal(x, x1) and np.array_equal(y, y1) and (k, a) == (k1, a1)
