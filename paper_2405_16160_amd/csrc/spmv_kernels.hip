@@ -17,7 +17,9 @@
 // the L2 to x: power-law A, n = 2e6, FP32 (x of 8 MB), 87.8 -> 85.1 us a product, Q
 // 92.9 -> 88.5; random n = 9e5, A, FP64 (7.2 MB) 93.7 -> 88.0.  Where x fits, the
 // hint costs the last-level cache's lines of the matrix: the same A', FP32 (x of 1.8
-// MB), 45.5 us without and 55.3 with it; at 4.8 MB the two are within 1 %.
+// MB), 45.5 us without and 55.3 with it; at 4.8 MB the two are within 1 %.  Without
+// the hint the steps of a full tile are unconditional (Q, n = 5e5, FP64, 20.0 -> 19.3
+// us, A 24.1 -> 23.4); with it the tests spread the loads and gain 1.5 %.
 #include "device.hpp"
 
 namespace pdhcg {
@@ -100,12 +102,15 @@ __global__ void __launch_bounds__(kStreamBlock) spmv_stream_kernel(const int32_t
     if (u * kStreamBlock > nr) break;
     rv[u] = gld(rowptr + r0 + min(u * kStreamBlock + tid, nr));
   }
-  if (ne > 0) {
+  // (kFull: the tile has entries for every step, none is looked at; a tile of a smaller
+  // matrix skips those that it does not have)
+  auto burst = [&](auto full) {
+    constexpr bool kFull = decltype(full)::value;
     int c[kStreamUnroll];
     V v[kStreamUnroll];
 #pragma unroll
     for (int u = 0; u < kStreamUnroll; ++u) {
-      if (u * kStreamBlock >= ne) break;
+      if (!kFull && u * kStreamBlock >= ne) break;
       const int k = min(u * kStreamBlock + tid, ne - 1);
       c[u] = NT ? gld_nt(col + e0 + k) : gld(col + e0 + k);
       v[u] = NT ? gld_nt(val + e0 + k) : gld(val + e0 + k);
@@ -113,16 +118,18 @@ __global__ void __launch_bounds__(kStreamBlock) spmv_stream_kernel(const int32_t
     double g[kStreamUnroll];
 #pragma unroll
     for (int u = 0; u < kStreamUnroll; ++u) {
-      if (u * kStreamBlock >= ne) break;
+      if (!kFull && u * kStreamBlock >= ne) break;
       g[u] = (double)gld(x + c[u]);
     }
 #pragma unroll
     for (int u = 0; u < kStreamUnroll; ++u) {
-      if (u * kStreamBlock >= ne) break;
+      if (!kFull && u * kStreamBlock >= ne) break;
       const int k = u * kStreamBlock + tid;
       if (k < ne) prod[k] = (double)v[u] * g[u];
     }
-  }
+  };
+  if (!NT && ne > (kStreamUnroll - 1) * kStreamBlock) burst(std::true_type{});
+  else if (ne > 0) burst(std::false_type{});
 #pragma unroll
   for (int u = 0; u < kStreamRowLoads; ++u) {
     if (u * kStreamBlock > nr) break;
